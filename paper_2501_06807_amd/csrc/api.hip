@@ -76,16 +76,30 @@ mpc_status launched(hipError_t e, const char* what) {
   return MPC_OK;
 }
 
+constexpr size_t kScratchBytes = (size_t)32 << 20;  // static array of mpc_static_evict_noalloc
+
 // Static eviction workspace: the (exponent offset, 1 / sum) pair of every window row, then fp32
-// token scores.
+// token scores, whose place the row pass's partials take before (they are merged by the time the first
+// score is written). `base` is what one split needs; splits are taken only as far as they leave a block
+// that fits the static array inside it, so that both entry points split alike.
 struct EvictWs {
-  size_t rowstat, score, total;
+  size_t rowstat, score, base, total;
+  int splits;
 };
-EvictWs evict_ws(const mpc_dims* d, int T, int W) {
+EvictWs evict_ws(const mpc_dims* d, int T, const mpc_evict_cfg* cfg) {
+  const int W = cfg->window;
   EvictWs w;
   w.rowstat = 0;
   w.score = align256((size_t)d->n_layers * d->batch * d->n_q_heads * W * sizeof(double));
-  w.total = w.score + align256((size_t)d->n_layers * d->batch * d->n_kv_heads * T * sizeof(float));
+  w.base = w.score + align256((size_t)d->n_layers * d->batch * d->n_kv_heads * T * sizeof(float));
+  const mpc::OwnerTable own = mpc::owner_table(d->layer0, d->n_layers, cfg->share_period, cfg->share_start);
+  const size_t heads = (size_t)own.n * d->batch * d->n_q_heads;
+  w.splits = own.n > 0 ? mpc::row_splits((int)heads, T, W, cfg->causal) : 1;
+  auto total = [&](int s) {
+    return s == 1 ? w.base : std::max(w.base, w.score + align256(heads * s * W * sizeof(double2)));
+  };
+  while (w.splits > 1 && w.base <= kScratchBytes && total(w.splits) > kScratchBytes) --w.splits;
+  w.total = total(w.splits);
   return w;
 }
 
@@ -152,7 +166,7 @@ size_t mpc_workspace_bytes(int32_t op, const mpc_dims* dims, int32_t T_or_Ts, co
   if (op == MPC_OP_STATIC_EVICT) {
     const mpc_evict_cfg* c = (const mpc_evict_cfg*)cfg;
     if (!c || c->window <= 0 || c->window > T_or_Ts) return 0;
-    return evict_ws(dims, T_or_Ts, c->window).total;
+    return evict_ws(dims, T_or_Ts, c).total;
   }
   if (op == MPC_OP_DECODE_ATTN) return decode_ws_bytes(dims);
   if (op == MPC_OP_DECODE_STEP) {
@@ -193,8 +207,8 @@ mpc_status prepare_evict(const mpc_dims* dims, int32_t T, const mpc_evict_cfg* c
     return fail(MPC_EUNSUPPORTED, "grid too large");
   int out_rows = 0;
   if ((s = cache_rows(dims, cfg->keep, &out_rows)) != MPC_OK) return s;
-  const EvictWs lay = evict_ws(dims, T, cfg->window);
-  if (!ws || ws_bytes < lay.total)
+  const EvictWs lay = evict_ws(dims, T, cfg);
+  if (!ws || ws_bytes < lay.base)
     return fail(MPC_EWORKSPACE, "static eviction needs %zu workspace bytes", lay.total);
 
   mpc::EvictArgs a{};
@@ -207,6 +221,8 @@ mpc_status prepare_evict(const mpc_dims* dims, int32_t T, const mpc_evict_cfg* c
   a.rowstat = (float2*)((char*)ws + lay.rowstat);
   a.score = token_score ? token_score : (float*)((char*)ws + lay.score);
   a.row_lse = row_lse;
+  a.part = (double2*)((char*)ws + lay.score);
+  a.splits = ws_bytes >= lay.total ? lay.splits : 1;
   a.B = dims->batch;
   a.layer0 = dims->layer0;
   a.n_layers = dims->n_layers;
@@ -665,7 +681,6 @@ mpc_status mpc_decode_step_status(void* ws, size_t ws_bytes, int32_t clear, int3
 // (hipGetSymbolAddress, with that device current) and only that address is handed to kernels.
 namespace {
 
-constexpr size_t kScratchBytes = (size_t)32 << 20;
 constexpr int kMaxDevices = 64;
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -710,7 +725,7 @@ mpc_status mpc_static_evict_noalloc(const mpc_dims* dims, int32_t T, const mpc_e
   mpc_status s = prepare_evict(dims, T, cfg, q_win, k, v, kept_idx, k_out, v_out, token_score, row_lse, nullptr, 0,
                                &unused);
   if (s != MPC_EWORKSPACE) return s;
-  const size_t need = evict_ws(dims, T, cfg->window).total;
+  const size_t need = evict_ws(dims, T, cfg).base;
   if (need > kScratchBytes)
     return fail(MPC_EWORKSPACE, "static eviction of this block needs %zu scratch bytes, the static array holds %zu "
                 "(call it on fewer layers or sequences)", need, kScratchBytes);

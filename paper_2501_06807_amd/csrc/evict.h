@@ -20,12 +20,20 @@ struct EvictArgs {
   float* score;        // [L][B][Hkv][T] accumulated attention (token_score or workspace)
   float2* rowstat;     // [L][B][Hq][W]: (whole-number offset b, every fma(c, score, b) <= 1; 1 / sum of exp2(fma(c, score, b)))
   float* row_lse;      // [L][B][Hq][W] natural log-sum-exp, optional
+  double2* part;       // row pass partials [owner heads][splits][W]: (sum, offset); unused with one split
+  int splits;          // workgroups that share a row block's keys
   int B, layer0, n_layers, Hq, Hkv, T, W, keep, local_keep, causal, period, start;
   int out_rows;        // row capacity of k_out / v_out per (layer, sequence, kv head)
   OwnerTable own;      // owner layers of the block
   uint64_t skip[kMaxLayers / 64];  // layers whose rows the gather leaves to the cluster build (bit l)
   float c32;           // fp32(sm_scale * log2(e)), the exponent scale of both scoring passes
 };
+
+constexpr int kMaxRowSplits = 16;
+constexpr int kSplitTiles = 6;  // what a split costs beside its tiles, in tiles
+
+// Workgroups per row block of the row pass for `heads` owner query heads.
+int row_splits(int heads, int T, int W, int causal);
 
 hipError_t launch_rowstats(const EvictArgs& a, int dtype, int D, hipStream_t st);
 hipError_t launch_colsum(const EvictArgs& a, int dtype, int D, hipStream_t st);

@@ -3,25 +3,26 @@
 // The accumulated attention of key j is A[j] = sum over the group's window rows t of
 // softmax_j(sm_scale * q_t . k_j). It needs every row's normaliser before any column can be
 // summed, so it takes two passes over the scores, both on the matrix cores (16-bit inputs:
-// v_mfma_f32_16x16x32_{bf16,f16} blocks; fp32 inputs: v_mfma_f32_32x32x2f32):
+// v_mfma_f32_32x32x16_{bf16,f16} in the row pass, 16x16x32 in the column pass; fp32 inputs:
+// v_mfma_f32_32x32x2f32):
 //   pass 1 (k_rowstats16, k_rowstats for fp32): window rows stay in registers as the B operand,
 //     key tiles stream through LDS as the A operand; each lane owns one query column of its
 //     blocks, so a row's sum needs no exchange until the end. Output per row: a whole-number
-//     offset b >= -ceil(fp32(c * m)) for the row max m with every exponent fma(c, s, b) at most 1
-//     (b = -ceil(fp32(c * m)) for fp32 inputs), and 1 / sum of exp2(fma(c, s, b)),
-//     c = fp32(sm_scale * log2(e)).
+//     offset b with every exponent fma(c, s, b) at most 5 (b = -ceil(fp32(c * m)) for fp32 inputs, m the
+//     row max), and 1 / sum of exp2(fma(c, s, b)), c = fp32(sm_scale * log2(e)). A row block's keys
+//     may be split over several workgroups (row_splits), whose sums k_rowmerge brings together.
 //   pass 2 (k_colsum16 for 16-bit inputs, k_colsum for fp32): keys stay in registers as the B
 //     operand, window-row tiles (all query heads of the group) stream through LDS as the A
 //     operand; each lane owns one key column, so the column sum needs no exchange within a tile.
 //     p = exp2(fma(c, s, b)) / sum, summed over a lane's rows of a tile in fp32 and accumulated
-//     across tiles in fp64. For 16-bit inputs both passes use 16x16 blocks and 64-row (64-key)
-//     tiles, so that each block's exponentials overlap the next block's matrix chain within the
-//     wave and a barrier serves 64 rows. Both passes form the exponent with one fused multiply-add
+//     across tiles in fp64. For 16-bit inputs both passes take 64-row (64-key) tiles, so that a
+//     barrier serves 64 rows. Both passes form the exponent with one fused multiply-add
 //     against the same offset, so the offset is a common factor of a row's terms and of its sum
-//     and cancels in p; it only has to keep every exponent at or below about 1. Being a whole
+//     and cancels in p; it only has to keep the exponents of the large terms small. Being a whole
 //     number, a move of the offset rescales pass 1's sums by an exact power of two (ldexp). The
-//     exponents of the terms near the max lie in (-1, 1], so their rounding, and that of c
-//     (proportional to |c * (s - m)|), stay smallest on the terms that carry the sums.
+//     exponents of the terms near the max lie in (-2, 5] (16-bit inputs; nearly always below 4), so
+//     their rounding, and that of c (proportional to |c * (s - m)|), stay smallest on the terms that
+//     carry the sums.
 // The top-k is a 4-pass, 8-bit LDS radix select on the fp32 score bits followed by an ordered
 // block compaction, each thread's run of scores held in registers up to 32K older tokens; the
 // gather copies kept rows with 16-byte lanes (all layers, or those whose representatives are not
@@ -110,22 +111,24 @@ struct Tile {
   static constexpr int BYTES = ROWS * RS;
 };
 
-// The PER 16-byte chunks a thread stages from each tile: chunk i is row row[i] of the
-// tile, at byte mem[i] from the tile's first row in memory and byte lds[i] of an LDS buffer. The
-// offsets are the same for every tile, so they are computed once per thread.
+// The PER 16-byte chunks a thread stages from each tile: chunk i is row row(i) of the tile, at byte
+// mem(i) from the tile's first row in memory and byte lds(i) of an LDS buffer. The threads cover whole
+// rows, so the chunks of a thread are a fixed number of rows apart: one offset each and constant strides
+// (one register instead of one per chunk; the row and column passes hold 168 at most).
 template <class TL, int NT>
 struct TileChunks {
-  unsigned row[TL::PER], mem[TL::PER], lds[TL::PER];
+  static_assert(NT % TL::CH == 0, "the threads cover whole rows");
+  static constexpr int STEP = NT / TL::CH;  // rows between a thread's chunks
   int tid;
+  unsigned row0, mem0, lds0;
   __device__ explicit TileChunks(int t) : tid(t) {
-#pragma unroll
-    for (int i = 0; i < TL::PER; ++i) {
-      const int ch = t + i * NT;
-      row[i] = ch / TL::CH;
-      mem[i] = row[i] * TL::RB + (ch % TL::CH) * 16;
-      lds[i] = row[i] * TL::RS + (ch % TL::CH) * 16;
-    }
+    row0 = t / TL::CH;
+    mem0 = row0 * TL::RB + (t % TL::CH) * 16;
+    lds0 = row0 * TL::RS + (t % TL::CH) * 16;
   }
+  __device__ int row(int i) const { return row0 + i * STEP; }
+  __device__ unsigned mem(int i) const { return mem0 + i * STEP * TL::RB; }
+  __device__ unsigned lds(int i) const { return lds0 + i * STEP * TL::RS; }
   // whether chunk i exists (always, when the threads cover the tile's chunks exactly)
   __device__ bool ok(int i) const { return (i + 1) * NT <= TL::CHUNKS || tid + i * NT < TL::CHUNKS; }
 };
@@ -143,6 +146,21 @@ struct PassShape {
 };
 static_assert(kRowBlock == kColBlockKeys, "both passes cover 256 rows / keys per workgroup");
 
+// A window row's statistics: offset o and sum L of exp2(fma(c, s, o)) over its visible keys.
+__device__ __forceinline__ void put_stat(const EvictArgs& a, size_t row, double L, float o) {
+  a.rowstat[row] = make_float2(o, (float)(1.0 / L));
+  // log-sum-exp of the scaled scores: log2 of sum exp2(c * s) = log2(L) - offset
+  if (a.row_lse) a.row_lse[row] = (float)((log2(L) - (double)o) * 0.69314718055994531);
+}
+
+// The same from one workgroup of owner head ou: final, or the partial of key split sp.
+__device__ __forceinline__ void put_row(const EvictArgs& a, int ou, size_t row0, int sp, int t, double L, float o) {
+  if (a.splits == 1)
+    put_stat(a, row0 + t, L, o);
+  else
+    a.part[((size_t)ou * a.splits + sp) * a.W + t] = make_double2(L, (double)o);
+}
+
 // Row pass on 32x32 matrix instructions (fp32 inputs; 16-bit inputs take k_rowstats16 below):
 // the offset follows the running max, so every exponent is at most 0.
 template <class DT, int D>
@@ -156,8 +174,8 @@ __global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) v
 
   const int n_rb = (a.W + kRowBlock - 1) / kRowBlock;
   const int id = xcd_remap(blockIdx.x, gridDim.x);
-  const int rb = id % n_rb;
-  const int ou = id / n_rb;  // (owner index * B + b) * Hq + hq
+  const int rb = id % n_rb, sp = id / n_rb % a.splits;
+  const int ou = id / n_rb / a.splits;  // (owner index * B + b) * Hq + hq
   const int l = a.own.local(ou / (a.B * a.Hq));
   const int b = (ou / a.Hq) % a.B, hq = ou % a.Hq;
   const size_t qunit = ((size_t)l * a.B + b) * a.Hq + hq;
@@ -182,7 +200,8 @@ __global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) v
   const char* kh = (const char*)a.k + kvunit * a.T * TL::RB;
   const int last_row = min(a.W - 1, rb * kRowBlock + kRowBlock - 1);
   const int jend = a.causal ? min(a.T, a.T - a.W + last_row + 1) : a.T;
-  const int ntile = (jend + 31) / 32;
+  const int ntile = (jend + 31) / 32, per = (ntile + a.splits - 1) / a.splits;
+  const int it0 = min(sp * per, ntile), it1 = min(it0 + per, ntile);  // this split's tiles
 
   const TileChunks<TL, NT> tc(tid);
   uint4 pre[TL::PER];
@@ -192,20 +211,22 @@ __global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) v
     if (tile * 32 + 32 <= a.T) {
 #pragma unroll
       for (int i = 0; i < TL::PER; ++i)
-        if (tc.ok(i)) pre[i] = ldg16(tb + tc.mem[i]);
+        if (tc.ok(i)) pre[i] = ldg16(tb + tc.mem(i));
     } else {
 #pragma unroll
       for (int i = 0; i < TL::PER; ++i)
-        pre[i] = tc.ok(i) && tile * 32 + (int)tc.row[i] < a.T ? ldg16(tb + tc.mem[i]) : make_uint4(0, 0, 0, 0);
+        pre[i] = tc.ok(i) && tile * 32 + tc.row(i) < a.T ? ldg16(tb + tc.mem(i)) : make_uint4(0, 0, 0, 0);
     }
   };
   auto stash = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < TL::PER; ++i)
-      if (tc.ok(i)) *(uint4*)&s_k[buf][tc.lds[i]] = pre[i];
+      if (tc.ok(i)) *(uint4*)&s_k[buf][tc.lds(i)] = pre[i];
   };
-  fetch(0);
-  stash(0);
+  if (it0 < it1) {
+    fetch(it0);
+    stash(0);
+  }
   // the row operands are in registers before the loop, so that no wait for them lands inside it
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
@@ -219,9 +240,9 @@ __global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) v
     nb[u] = INFINITY;
     ell[u] = 0.0;
   }
-  for (int it = 0; it < ntile; ++it) {
-    const int buf = it & 1;
-    if (it + 1 < ntile) fetch(it + 1);
+  for (int it = it0; it < it1; ++it) {
+    const int buf = (it - it0) & 1;
+    if (it + 1 < it1) fetch(it + 1);
     f32x16 acc[NBK] = {};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -267,7 +288,7 @@ __global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) v
       }
       ell[u] += (double)ps;
     }
-    if (it + 1 < ntile) stash(buf ^ 1);
+    if (it + 1 < it1) stash(buf ^ 1);
     __syncthreads();
   }
 #pragma unroll
@@ -279,11 +300,7 @@ __global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) v
     double L = 0.0;
     if (ell[u] > 0.0) L += ldexp(ell[u], (int)(nbx - nb[u]));
     if (eo > 0.0) L += ldexp(eo, (int)(nbx - nbo));
-    if (hl == 0 && t[u] < a.W) {
-      a.rowstat[(size_t)qunit * a.W + t[u]] = make_float2(nbx, (float)(1.0 / L));
-      // log-sum-exp of the scaled scores: log2 of sum exp2(c * s) = log2(L) - offset
-      if (a.row_lse) a.row_lse[(size_t)qunit * a.W + t[u]] = (float)((log2(L) - (double)nbx) * 0.69314718055994531);
-    }
+    if (hl == 0 && t[u] < a.W) put_row(a, ou, (size_t)qunit * a.W, sp, t[u], L, nbx);
   }
 }
 
@@ -340,11 +357,11 @@ __global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) v
     if (ft0 + 32 <= a.W) {
 #pragma unroll
       for (int i = 0; i < TL::PER; ++i)
-        if (tc.ok(i)) pre[i] = ldg16(tb + tc.mem[i]);
+        if (tc.ok(i)) pre[i] = ldg16(tb + tc.mem(i));
     } else {
 #pragma unroll
       for (int i = 0; i < TL::PER; ++i)
-        pre[i] = tc.ok(i) && ft0 + (int)tc.row[i] < a.W ? ldg16(tb + tc.mem[i]) : make_uint4(0, 0, 0, 0);
+        pre[i] = tc.ok(i) && ft0 + tc.row(i) < a.W ? ldg16(tb + tc.mem(i)) : make_uint4(0, 0, 0, 0);
     }
     if (tid < 32) pre_b = ft0 + tid < a.W ? a.rowstat[r0 + tid] : make_float2(0.f, 0.f);
     ft0 += 32;
@@ -356,7 +373,7 @@ __global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) v
   auto stash = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < TL::PER; ++i)
-      if (tc.ok(i)) *(uint4*)&s_q[buf][tc.lds[i]] = pre[i];
+      if (tc.ok(i)) *(uint4*)&s_q[buf][tc.lds(i)] = pre[i];
     if (tid < 32) {
       s_nb[buf][tid] = pre_b.x;
       s_il[buf][tid] = pre_b.y;
@@ -430,54 +447,95 @@ __global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) v
   }
 }
 
-// Row pass for 16-bit inputs on 16x16x32 matrix instructions. A wave holds 64 window rows in
-// registers as four 16-row B operands (query groups) and takes each 64-key tile from LDS as four
-// 16-key A operands, so a tile is sixteen 16x16 blocks; a lane holds keys 4 (lane / 16) + r of one
-// row per block. Each block's exponentials are taken against the row's current offset, with no
-// running max, beside the next block's matrix chain (one basic block, so the two interleave). A
-// block whose four terms sum to at most 2 has every exponent at most 1, as accurate as an offset
-// at the max; a larger sum takes the slow path: the offset moves to the block's max if that is
-// higher (the running sums rescaled by an exact power of two) and the block is summed again. The
-// four lanes of a row meet once at the end at the smallest offset, so no exponent of pass 2 exceeds 1.
+// The vector work of one 32x32 block of scores (sixteen per lane), in nine chunks: F(r) forms the
+// exponent of score r, E(r) takes its exp2, A(r) adds it up. Chunk 0 opens the block (three
+// operations), chunks 1..7 carry two scores each (six operations, the exp2s apart from one another and
+// from their uses), chunk 8 closes it. Every chunk ends with a scheduling barrier, so the chunks stay
+// where the caller writes them between another block's matrix instructions.
+template <int CHUNK, class F, class E, class A>
+__device__ __forceinline__ void block_chunk(F f, E e, A add) {
+  if constexpr (CHUNK == 0) {
+    f(0);
+    f(1);
+    e(0);
+  } else if constexpr (CHUNK < 8) {
+    e(2 * CHUNK - 1);
+    f(2 * CHUNK);
+    f(2 * CHUNK + 1);
+    e(2 * CHUNK);
+    add(2 * CHUNK - 2);
+    add(2 * CHUNK - 1);
+  } else {
+    e(15);
+    add(14);
+    add(15);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Keeps a value computed here from being moved to its use.
+__device__ __forceinline__ void pin(float& x) { asm volatile("" : "+v"(x)); }
+
+// Row pass for 16-bit inputs, on 32x32x16 matrix instructions. A wave holds 64 window rows in
+// registers as two 32-row B operands and takes each 64-key tile from LDS as two 32-key A operands: four
+// 32x32 blocks, whose vector work (fma, exp2, add for each of a lane's sixteen scores of one row) runs
+// between the matrix instructions of the block after it, in the order written out below. Left to the
+// compiler, a block's chain and its exponentials follow one another with idle cycles between, and the
+// 16x16x32 instruction costs twice the issue time for the same work: in a register-only loop with three
+// waves per SIMD, 64 scores take 8.9 ns this way, 10.7 ns with 16x16x32 instructions.
+//
+// The exponents are taken against an offset set from the wave's first tile, one below that tile's row
+// max, and kept while the largest terms of a tile stay within 2^5: a tile in which a lane's 32 terms of a
+// row sum to more than 32 is done again after its maxima have moved the offset (its scores still in LDS;
+// about one tile in a hundred on random prompts of 32K keys). So no per-block test splits the loop.
+//
+// What bounds it: the chip's power. At 4 x 32768 keys and 32 heads the matrix cores are busy 64% of the
+// cycles, at 1.8 GHz (52% at 2.0 GHz with 16x16x32 blocks and a test per block): 3.90 -> 3.50 ms, and
+// 3.25 ms with the keys split in two, 1.03 PFLOP/s beside a bf16 matrix product's 1.32 on this card.
+// Short of work for every compute unit (row_splits), the splits count for more: 32 heads of 7177 keys
+// 220 -> 148 us, 100 us split in four.
 template <class DT, int D>
 __global__ __launch_bounds__(kRowThreads16, 3) void k_rowstats16(EvictArgs a) {
+  using M = Mma<DT>;
   constexpr int NT = kRowThreads16;
   constexpr int KT = 64;  // keys per staged tile
   using TL = Tile<DT, D, NT, KT>;
-  constexpr int KS = D / 32;
+  constexpr int KS = D / 16;
   static_assert(DT::kElt == 2, "16-bit inputs");
   static_assert(NT / kWave * 64 == kRowBlock, "four waves of 64 rows");
   __shared__ __align__(16) unsigned char s_k[2][TL::BYTES];
 
   const int n_rb = (a.W + kRowBlock - 1) / kRowBlock;
   const int id = xcd_remap(blockIdx.x, gridDim.x);
-  const int rb = id % n_rb;
-  const int ou = id / n_rb;  // (owner index * B + b) * Hq + hq
+  const int rb = id % n_rb, sp = id / n_rb % a.splits;
+  const int ou = id / n_rb / a.splits;  // (owner index * B + b) * Hq + hq
   const int l = a.own.local(ou / (a.B * a.Hq));
   const int b = (ou / a.Hq) % a.B, hq = ou % a.Hq;
   const size_t qunit = ((size_t)l * a.B + b) * a.Hq + hq;
   const int G = a.Hq / a.Hkv;
   const size_t kvunit = ((size_t)l * a.B + b) * a.Hkv + hq / G;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, c16 = lane & 15, q4 = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, c32 = lane & 31, hl = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform over the wave
 
-  // query group g of this wave holds window rows row0 + 16 g + lane % 16
+  // row block u of this wave holds window rows row0 + 32 u + lane % 32
   const int row0 = rb * kRowBlock + w * 64;
-  int t[4], pos[4];
-  uint4 qf[4][KS];
+  int t[2], last[2];  // last key each row sees
+  uint4 qf[2][KS];
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    t[g] = row0 + 16 * g + c16;
-    const int tc = t[g] < a.W ? t[g] : a.W - 1;
-    pos[g] = a.T - a.W + tc;
+  for (int u = 0; u < 2; ++u) {
+    t[u] = row0 + 32 * u + c32;
+    const int tc = t[u] < a.W ? t[u] : a.W - 1;
+    last[u] = a.causal ? a.T - a.W + tc : a.T - 1;
     const char* qrow = (const char*)a.q_win + ((size_t)qunit * a.W + tc) * TL::RB;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[g][ks] = ldg16(qrow + (ks * 32 + q4 * 8) * DT::kElt);
+    for (int ks = 0; ks < KS; ++ks) qf[u][ks] = ldg16(qrow + ks * 32 + hl * 16);
   }
 
   const char* kh = (const char*)a.k + kvunit * a.T * TL::RB;
   const int last_row = min(a.W - 1, rb * kRowBlock + kRowBlock - 1);
   const int jend = a.causal ? min(a.T, a.T - a.W + last_row + 1) : a.T;
-  const int ntile = (jend + KT - 1) / KT;
+  const int ntile = (jend + KT - 1) / KT, per = (ntile + a.splits - 1) / a.splits;
+  const int it0 = min(sp * per, ntile), it1 = min(it0 + per, ntile);  // this split's tiles
 
   const TileChunks<TL, NT> tc(tid);
   uint4 pre[TL::PER];
@@ -487,130 +545,169 @@ __global__ __launch_bounds__(kRowThreads16, 3) void k_rowstats16(EvictArgs a) {
     if (tile * KT + KT <= a.T) {
 #pragma unroll
       for (int i = 0; i < TL::PER; ++i)
-        if (tc.ok(i)) pre[i] = ldg16(tb + tc.mem[i]);
+        if (tc.ok(i)) pre[i] = ldg16(tb + tc.mem(i));
     } else {
 #pragma unroll
       for (int i = 0; i < TL::PER; ++i)
-        pre[i] = tc.ok(i) && tile * KT + (int)tc.row[i] < a.T ? ldg16(tb + tc.mem[i]) : make_uint4(0, 0, 0, 0);
+        pre[i] = tc.ok(i) && tile * KT + tc.row(i) < a.T ? ldg16(tb + tc.mem(i)) : make_uint4(0, 0, 0, 0);
     }
   };
   auto stash = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < TL::PER; ++i)
-      if (tc.ok(i)) *(uint4*)&s_k[buf][tc.lds[i]] = pre[i];
+      if (tc.ok(i)) *(uint4*)&s_k[buf][tc.lds(i)] = pre[i];
   };
-  fetch(0);
-  stash(0);
+  if (it0 < it1) {
+    fetch(it0);
+    stash(0);
+  }
   // the row operands are in registers before the loop, so that no wait for them lands inside it
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 
   const float cf = a.c32;
-  float nb[4];    // whole-number offset of each query group's row (this lane's keys)
-  double ell[4];  // sum of exp2(fma(c, s, nb)) so far
+  float nb[2] = {INFINITY, INFINITY};  // whole-number offset of each block's row (the same in both half-waves)
+  double ell[2] = {0.0, 0.0};          // this lane's sum of exp2(fma(c, s, nb)) so far
+  auto operand = [&](const unsigned char* kb, int ks) { return __builtin_bit_cast(typename M::Op, *(const uint4*)(kb + ks * 32)); };
+  auto rows = [&](int u, int ks) { return __builtin_bit_cast(typename M::Op, qf[u][ks]); };
+
+  // sums of a tile whose every key is visible to every row of the wave
+  auto sum_full = [&](int buf, float (&ps)[2]) {
+    f32x16 acc[2];
+    typename M::Op af[KS];
+    float x[2][16], pa[2] = {0.f, 0.f}, pb[2] = {0.f, 0.f};
+    const unsigned char* kb = &s_k[buf][c32 * TL::RS + hl * 16];
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    nb[g] = INFINITY;
-    ell[g] = 0.0;
-  }
-  // one tile; block b = (key quarter b / 4, query group b % 4). FULL: every key of the tile visible
-  // to every row of the wave
-  auto tile = [&](auto full_tag, int buf, int j0) {
-    constexpr bool FULL = decltype(full_tag)::value;
-    float psg[4] = {0.f, 0.f, 0.f, 0.f};
-    uint4 af[KS];
-    auto load_af = [&](int kq) {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        af[ks] = *(const uint4*)&s_k[buf][(16 * kq + c16) * TL::RS + (ks * 32 + q4 * 8) * DT::kElt];
+    for (int ks = 0; ks < KS; ++ks) af[ks] = operand(kb, ks);
+    __builtin_amdgcn_sched_barrier(0);
+    auto vec = [&](auto chunk, int j) {  // chunk of block j
+      if (j < 0 || j >= KT / 16) return;
+      const int u = j & 1;
+      block_chunk<decltype(chunk)::value>([&](int r) { x[u][r] = fmaf(cf, acc[u][r], nb[u]); pin(x[u][r]); },
+                                          [&](int r) { x[u][r] = fast_exp2(x[u][r]); pin(x[u][r]); },
+                                          [&](int r) {
+                                            float& p = r & 1 ? pb[u] : pa[u];
+                                            p += x[u][r];
+                                            pin(p);
+                                          });
     };
-    auto chain = [&](int g) {
-      f32x4 c = {0.f, 0.f, 0.f, 0.f};
+    // block b = (key half b / 2, row block b % 2)
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) c = mma16<DT>(af[ks], qf[g][ks], c);
-      return c;
-    };
-    auto visible = [&](int kq, int g, int r) {
-      if constexpr (FULL) return true;
-      const int j = j0 + 16 * kq + 4 * q4 + r;
-      return j < a.T && (!a.causal || j <= pos[g]);
-    };
-    auto sum4 = [&](const f32x4& c, int kq, int g) {
-      float ps = 0.f;
+    for (int b = 0; b < KT / 16 + 2; ++b) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (visible(kq, g, r)) ps += fast_exp2(fmaf(cf, c[r], nb[g]));
-      return ps;
-    };
-    auto finish = [&](const f32x4& c, int kq, int g, float ps) {
-      if (ps > 2.f) {  // an exponent may exceed 1 (or the row's first terms): offset at the max
-        float tmax = -INFINITY;
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (visible(kq, g, r)) tmax = fmaxf(tmax, c[r]);
-        const float nb_new = -ceilf(cf * tmax);
-        if (nb_new < nb[g]) {
-          const int d = (int)(nb_new - nb[g]);
-          if (ell[g] > 0.0) ell[g] = ldexp(ell[g], d);
-          if (psg[g] > 0.f) psg[g] = ldexpf(psg[g], d);
-          nb[g] = nb_new;
+      for (int ks = 0; ks < KS; ++ks) {
+        if (b < KT / 16) {
+          acc[b & 1] = M::run(af[ks], rows(b & 1, ks), ks ? acc[b & 1] : f32x16{});
+          if ((b & 1) && b + 1 < KT / 16) af[ks] = operand(kb + 32 * (b / 2 + 1) * TL::RS, ks);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        ps = sum4(c, kq, g);
+        using std::integral_constant;
+        if (ks == 0) vec(integral_constant<int, 8>{}, b - 2);
+        if constexpr (KS == 8) {
+          if (ks == 0) vec(integral_constant<int, 0>{}, b - 1);
+          if (ks == 1) vec(integral_constant<int, 1>{}, b - 1);
+          if (ks == 2) vec(integral_constant<int, 2>{}, b - 1);
+          if (ks == 3) vec(integral_constant<int, 3>{}, b - 1);
+          if (ks == 4) vec(integral_constant<int, 4>{}, b - 1);
+          if (ks == 5) vec(integral_constant<int, 5>{}, b - 1);
+          if (ks == 6) vec(integral_constant<int, 6>{}, b - 1);
+          if (ks == 7) vec(integral_constant<int, 7>{}, b - 1);
+        } else {
+          if (ks == 0) vec(integral_constant<int, 0>{}, b - 1), vec(integral_constant<int, 1>{}, b - 1);
+          if (ks == 1) vec(integral_constant<int, 2>{}, b - 1), vec(integral_constant<int, 3>{}, b - 1);
+          if (ks == 2) vec(integral_constant<int, 4>{}, b - 1), vec(integral_constant<int, 5>{}, b - 1);
+          if (ks == 3) vec(integral_constant<int, 6>{}, b - 1), vec(integral_constant<int, 7>{}, b - 1);
+        }
       }
-      psg[g] += ps;
-    };
-    load_af(0);
-    f32x4 cp = chain(0);
-#pragma unroll
-    for (int bb = 1; bb < 4 * (KT / 16); ++bb) {
-      if ((bb & 3) == 0) load_af(bb >> 2);
-      const f32x4 cc = chain(bb & 3);
-      const int kp = (bb - 1) >> 2, gp = (bb - 1) & 3;
-      finish(cp, kp, gp, sum4(cp, kp, gp));
-      cp = cc;
     }
-    finish(cp, KT / 16 - 1, 3, sum4(cp, KT / 16 - 1, 3));
 #pragma unroll
-    for (int g = 0; g < 4; ++g) ell[g] += (double)psg[g];
+    for (int u = 0; u < 2; ++u) ps[u] = pa[u] + pb[u];
   };
-  // a wave whose rows all lie past the window (the last workgroup of a ragged window) only helps
-  // stage the tiles
-  const bool rows_live = row0 < a.W;
-  for (int it = 0; it < ntile; ++it) {
-    const int buf = it & 1;
-    if (it + 1 < ntile) fetch(it + 1);
-    const int j0 = it * KT;
-    if (rows_live) {
-      if (j0 + KT - 1 < a.T && (!a.causal || j0 + KT - 1 <= a.T - a.W + row0))
-        tile(std::true_type{}, buf, j0);
-      else
-        tile(std::false_type{}, buf, j0);
+  // any tile, one block after the other: f(u, r, score, visible) for every score
+  auto each = [&](int buf, int j0, auto f) {
+#pragma unroll 1
+    for (int h = 0; h < KT / 32; ++h) {
+      const unsigned char* kb = &s_k[buf][(32 * h + c32) * TL::RS + hl * 16];
+      f32x16 acc[2] = {};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const typename M::Op af = operand(kb, ks);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) acc[u] = M::run(af, rows(u, ks), acc[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int j = j0 + 32 * h + acc_row(r, lane);
+          f(u, acc[u][r], j <= last[u]);
+        }
     }
-    if (it + 1 < ntile) stash(buf ^ 1);
+  };
+  // moves the offsets one below the tile's largest exponents, where that lowers them
+  auto set_offsets = [&](int buf, int j0) {
+    float mx[2] = {-INFINITY, -INFINITY};
+    each(buf, j0, [&](int u, float s, bool seen) { mx[u] = fmaxf(mx[u], seen ? s : -INFINITY); });
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      mx[u] = fmaxf(mx[u], __shfl_xor(mx[u], 32));
+      const float to = -ceilf(cf * mx[u]) - 1.f;
+      if (to < nb[u]) {
+        if (ell[u] > 0.0) ell[u] = ldexp(ell[u], (int)(to - nb[u]));
+        nb[u] = to;
+      }
+    }
+  };
+  bool fresh = true;  // no offsets yet
+  for (int it = it0; it < it1; ++it) {
+    const int buf = (it - it0) & 1;
+    if (it + 1 < it1) fetch(it + 1);
+    const int j0 = it * KT;
+    // a wave none of whose rows sees the tile (rows past a ragged window, keys after its last row) only
+    // helps stage it
+    if (row0 < a.W && (!a.causal || j0 <= a.T - a.W + row0 + 63)) {
+      const bool full = j0 + KT - 1 < a.T && (!a.causal || j0 + KT - 1 <= a.T - a.W + row0);
+      float ps[2];
+      for (bool again = fresh;;) {
+        if (again) set_offsets(buf, j0);
+        if (full) {
+          sum_full(buf, ps);
+        } else {
+          ps[0] = ps[1] = 0.f;
+          each(buf, j0, [&](int u, float s, bool seen) { ps[u] += seen ? fast_exp2(fmaf(cf, s, nb[u])) : 0.f; });
+        }
+        if (again || !__any(ps[0] > 32.f || ps[1] > 32.f)) break;
+        again = true;
+      }
+      fresh = false;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) ell[u] += (double)ps[u];
+    }
+    if (it + 1 < it1) stash(buf ^ 1);
     __syncthreads();
   }
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    // the four lanes of a row (lane % 16 equal) meet at the smallest offset, in two pairwise steps
-    double e = ell[g];
-    float o = nb[g];
-#pragma unroll
-    for (int x = 16; x <= 32; x <<= 1) {
-      const double eo = __shfl_xor(e, x);
-      const float oo = __shfl_xor(o, x);
-      const float ox = fminf(o, oo);
-      double L = 0.0;
-      if (e > 0.0) L += ldexp(e, (int)(ox - o));
-      if (eo > 0.0) L += ldexp(eo, (int)(ox - oo));
-      e = L;
-      o = ox;
-    }
-    if (q4 == 0 && t[g] < a.W) {
-      a.rowstat[(size_t)qunit * a.W + t[g]] = make_float2(o, (float)(1.0 / e));
-      // log-sum-exp of the scaled scores: log2 of sum exp2(c * s) = log2(L) - offset
-      if (a.row_lse) a.row_lse[(size_t)qunit * a.W + t[g]] = (float)((log2(e) - (double)o) * 0.69314718055994531);
-    }
+  for (int u = 0; u < 2; ++u) {
+    const double e = ell[u] + __shfl_xor(ell[u], 32);
+    if (hl == 0 && t[u] < a.W) put_row(a, ou, (size_t)qunit * a.W, sp, t[u], e, nb[u]);
   }
+}
+
+// Statistics of the window rows whose keys were split over several workgroups: the splits' sums meet at the
+// smallest offset. A split none of whose keys the row sees holds a zero sum at an infinite offset.
+__global__ __launch_bounds__(256) void k_rowmerge(EvictArgs a) {
+  const int64_t n = (int64_t)a.own.n * a.B * a.Hq * a.W, i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int ou = (int)(i / a.W), t = (int)(i % a.W);
+  const double2* p = a.part + (size_t)ou * a.splits * a.W + t;
+  double o = INFINITY, L = 0.0;
+  for (int s = 0; s < a.splits; ++s) o = fmin(o, p[(size_t)s * a.W].y);
+  for (int s = 0; s < a.splits; ++s) {
+    const double2 x = p[(size_t)s * a.W];
+    if (x.x > 0.0) L += ldexp(x.x, (int)(o - x.y));
+  }
+  const size_t unit = (size_t)a.own.local(ou / (a.B * a.Hq)) * a.B * a.Hq + ou % (a.B * a.Hq);
+  put_stat(a, unit * a.W + t, L, (float)o);
 }
 
 // Column pass for 16-bit inputs on 16x16x32 matrix instructions. A wave holds 64 keys in
@@ -673,11 +770,11 @@ __global__ __launch_bounds__(kColThreads16, 3) void k_colsum16(EvictArgs a) {
     if (ft0 + RT <= a.W) {
 #pragma unroll
       for (int i = 0; i < TL::PER; ++i)
-        if (tc.ok(i)) pre[i] = ldg16(tb + tc.mem[i]);
+        if (tc.ok(i)) pre[i] = ldg16(tb + tc.mem(i));
     } else {
 #pragma unroll
       for (int i = 0; i < TL::PER; ++i)
-        pre[i] = tc.ok(i) && ft0 + (int)tc.row[i] < a.W ? ldg16(tb + tc.mem[i]) : make_uint4(0, 0, 0, 0);
+        pre[i] = tc.ok(i) && ft0 + tc.row(i) < a.W ? ldg16(tb + tc.mem(i)) : make_uint4(0, 0, 0, 0);
     }
     if (tid < RT) pre_b = ft0 + tid < a.W ? a.rowstat[r0 + tid] : make_float2(0.f, 0.f);
     ft0 += RT;
@@ -689,7 +786,7 @@ __global__ __launch_bounds__(kColThreads16, 3) void k_colsum16(EvictArgs a) {
   auto stash = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < TL::PER; ++i)
-      if (tc.ok(i)) *(uint4*)&s_q[buf][tc.lds[i]] = pre[i];
+      if (tc.ok(i)) *(uint4*)&s_q[buf][tc.lds(i)] = pre[i];
     if (tid < RT) {
       s_nb[buf][tid] = pre_b.x;
       s_il[buf][tid] = pre_b.y;
@@ -1002,9 +1099,9 @@ hipError_t launch_pass(const EvictArgs& a, bool rows, hipStream_t st) {
   if (rows) {
     const int n_rb = (a.W + kRowBlock - 1) / kRowBlock;
     if constexpr (DT::kElt == 2)
-      hipLaunchKernelGGL((k_rowstats16<DT, D>), dim3(a.own.n * a.B * a.Hq * n_rb), dim3(kRowThreads16), 0, st, a);
+      hipLaunchKernelGGL((k_rowstats16<DT, D>), dim3(a.own.n * a.B * a.Hq * n_rb * a.splits), dim3(kRowThreads16), 0, st, a);
     else
-      hipLaunchKernelGGL((k_rowstats<DT, D>), dim3(a.own.n * a.B * a.Hq * n_rb), dim3(PassShape<DT>::THREADS), 0, st, a);
+      hipLaunchKernelGGL((k_rowstats<DT, D>), dim3(a.own.n * a.B * a.Hq * n_rb * a.splits), dim3(PassShape<DT>::THREADS), 0, st, a);
   } else {
     const int n_kb = (a.T + kColBlockKeys - 1) / kColBlockKeys;
     if constexpr (DT::kElt == 2)
@@ -1034,7 +1131,34 @@ hipError_t launch_pass_any(const EvictArgs& a, int dtype, int D, bool rows, hipS
 }  // namespace
 
 hipError_t launch_rowstats(const EvictArgs& a, int dtype, int D, hipStream_t st) {
-  return launch_pass_any(a, dtype, D, true, st);
+  const hipError_t e = launch_pass_any(a, dtype, D, true, st);
+  if (e != hipSuccess || a.splits == 1) return e;
+  const int64_t rows = (int64_t)a.own.n * a.B * a.Hq * a.W;
+  hipLaunchKernelGGL(k_rowmerge, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+// A split is taken where it evens out the work: the launch ends with the compute unit that holds the most
+// workgroups (one alone on its unit runs at about 1.4 times the time of one among several), and each split
+// costs about six tiles beside its own: its rows' loads, and the first tile three times over for the offsets.
+// 32 heads of 7177 keys (192 row blocks): 148 us unsplit, 100 us in four; 84 heads of 2048 keys (168):
+// 37 and 25 us in three; 128 heads of 32768 keys (1664 = 6.5 a unit): 3.50 and 3.25 ms in two. 320 heads
+// of 8192 keys (8.75 a unit) stay whole.
+int row_splits(int heads, int T, int W, int causal) {
+  const int64_t base = (int64_t)heads * ((W + kRowBlock - 1) / kRowBlock);
+  const int ntile = ((causal ? T - W / 2 : T) + 63) / 64;
+  int best = 1;
+  double cost = INFINITY;
+  for (int s = 1; s <= kMaxRowSplits && s <= ntile; ++s) {
+    const int64_t per_cu = (base * s + kNumCU - 1) / kNumCU;
+    const double len = (double)((ntile + s - 1) / s) + kSplitTiles;
+    const double c = per_cu == 1 ? 1.4 * len : per_cu * len;
+    if (c < 0.97 * cost) {
+      cost = c;
+      best = s;
+    }
+  }
+  return best;
 }
 
 hipError_t launch_colsum(const EvictArgs& a, int dtype, int D, hipStream_t st) {
