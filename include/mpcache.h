@@ -130,9 +130,7 @@ size_t mpc_workspace_bytes(int32_t op, const mpc_dims* dims, int32_t T_or_Ts, co
  *   token_score [L][B][Hkv][T] float, optional out (NULL = not returned); owner layers only
  *   row_lse     [L][B][Hq][W] float, optional out: natural log-sum-exp of each window row's
  *               scaled scores (the softmax normaliser); owner layers only
- *   ws          workspace of mpc_workspace_bytes(MPC_OP_STATIC_EVICT, dims, T, cfg) bytes. A smaller
- *               one of 8 bytes per window row plus 4 per token (each rounded up to 256) serves too, with
- *               the keys of a window row summed by one workgroup, which may change results in rounding.
+ *   ws          workspace of mpc_workspace_bytes(MPC_OP_STATIC_EVICT, dims, T, cfg) bytes.
  * Accumulation: fp32 matrix-core dot products; each exponent is one fp32 fused multiply-add
  * against a per-row whole-number offset that keeps every exponent at most 5, shared by the row sum
  * and the column sums; sums of at most 16 terms in fp32 (two of them added per tile in the row sums),

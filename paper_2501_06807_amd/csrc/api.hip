@@ -80,10 +80,10 @@ constexpr size_t kScratchBytes = (size_t)32 << 20;  // static array of mpc_stati
 
 // Static eviction workspace: the (exponent offset, 1 / sum) pair of every window row, then fp32
 // token scores, whose place the row pass's partials take before (they are merged by the time the first
-// score is written). `base` is what one split needs; splits are taken only as far as they leave a block
-// that fits the static array inside it, so that both entry points split alike.
+// score is written). Splits are taken only as far as a block that fits the static array with one split
+// stays inside it: no block is refused for its splits, and both entry points split alike.
 struct EvictWs {
-  size_t rowstat, score, base, total;
+  size_t rowstat, score, total;
   int splits;
 };
 EvictWs evict_ws(const mpc_dims* d, int T, const mpc_evict_cfg* cfg) {
@@ -91,14 +91,14 @@ EvictWs evict_ws(const mpc_dims* d, int T, const mpc_evict_cfg* cfg) {
   EvictWs w;
   w.rowstat = 0;
   w.score = align256((size_t)d->n_layers * d->batch * d->n_q_heads * W * sizeof(double));
-  w.base = w.score + align256((size_t)d->n_layers * d->batch * d->n_kv_heads * T * sizeof(float));
+  const size_t base = w.score + align256((size_t)d->n_layers * d->batch * d->n_kv_heads * T * sizeof(float));
   const mpc::OwnerTable own = mpc::owner_table(d->layer0, d->n_layers, cfg->share_period, cfg->share_start);
   const size_t heads = (size_t)own.n * d->batch * d->n_q_heads;
   w.splits = own.n > 0 ? mpc::row_splits((int)heads, T, W, cfg->causal) : 1;
   auto total = [&](int s) {
-    return s == 1 ? w.base : std::max(w.base, w.score + align256(heads * s * W * sizeof(double2)));
+    return s == 1 ? base : std::max(base, w.score + align256(heads * s * W * sizeof(double2)));
   };
-  while (w.splits > 1 && w.base <= kScratchBytes && total(w.splits) > kScratchBytes) --w.splits;
+  while (w.splits > 1 && base <= kScratchBytes && total(w.splits) > kScratchBytes) --w.splits;
   w.total = total(w.splits);
   return w;
 }
@@ -208,7 +208,7 @@ mpc_status prepare_evict(const mpc_dims* dims, int32_t T, const mpc_evict_cfg* c
   int out_rows = 0;
   if ((s = cache_rows(dims, cfg->keep, &out_rows)) != MPC_OK) return s;
   const EvictWs lay = evict_ws(dims, T, cfg);
-  if (!ws || ws_bytes < lay.base)
+  if (!ws || ws_bytes < lay.total)
     return fail(MPC_EWORKSPACE, "static eviction needs %zu workspace bytes", lay.total);
 
   mpc::EvictArgs a{};
@@ -222,7 +222,7 @@ mpc_status prepare_evict(const mpc_dims* dims, int32_t T, const mpc_evict_cfg* c
   a.score = token_score ? token_score : (float*)((char*)ws + lay.score);
   a.row_lse = row_lse;
   a.part = (double2*)((char*)ws + lay.score);
-  a.splits = ws_bytes >= lay.total ? lay.splits : 1;
+  a.splits = lay.splits;
   a.B = dims->batch;
   a.layer0 = dims->layer0;
   a.n_layers = dims->n_layers;
@@ -725,7 +725,7 @@ mpc_status mpc_static_evict_noalloc(const mpc_dims* dims, int32_t T, const mpc_e
   mpc_status s = prepare_evict(dims, T, cfg, q_win, k, v, kept_idx, k_out, v_out, token_score, row_lse, nullptr, 0,
                                &unused);
   if (s != MPC_EWORKSPACE) return s;
-  const size_t need = evict_ws(dims, T, cfg).base;
+  const size_t need = evict_ws(dims, T, cfg).total;
   if (need > kScratchBytes)
     return fail(MPC_EWORKSPACE, "static eviction of this block needs %zu scratch bytes, the static array holds %zu "
                 "(call it on fewer layers or sequences)", need, kScratchBytes);
