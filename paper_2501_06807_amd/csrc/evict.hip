@@ -718,6 +718,12 @@ __global__ __launch_bounds__(256) void k_rowmerge(EvictArgs a) {
 // a barrier, a tile load and a row-statistics stash serve 64 rows. A lane holds rows
 // 4 (lane / 16) + r of one key per block; its fp32 sum over a tile's sixteen rows goes into an fp64
 // total, and the four lanes of a key meet once at the end.
+// What bounds it: the chip's power, as for the row pass (4 x 32768 keys, 32 heads: 3.3 ms, the matrix cores
+// busy 52% at 1.95 GHz). So the row pass's written-out order changes nothing here (fewer cycles at a lower
+// clock; 8192 keys to 131072 within 0.3%), and 32x32x16 blocks, which need 222 registers with the row
+// statistics of their sixteen rows a lane, are slower (two waves per SIMD: 3.7 against 3.3 ms). Quarters of a
+// masked tile that no key of the wave is seen by, or past the window, are left out: of a window of 204 rows
+// the last tile holds 12 (8 x 1024 keys, 17 owner layers: 490 -> 467 us).
 template <class DT, int D>
 __global__ __launch_bounds__(kColThreads16, 3) void k_colsum16(EvictArgs a) {
   constexpr int NT = kColThreads16;
@@ -737,7 +743,8 @@ __global__ __launch_bounds__(kColThreads16, 3) void k_colsum16(EvictArgs a) {
   const int b = (ou / a.Hkv) % a.B, h = ou % a.Hkv;
   const size_t kvunit = ((size_t)l * a.B + b) * a.Hkv + h;
   const int G = a.Hq / a.Hkv;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, c16 = lane & 15, q4 = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, q4 = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform over the wave
 
   // key group g of this wave holds keys jw + 16 g + lane % 16
   const int jw = kb * kColBlockKeys + w * 64;
@@ -806,6 +813,9 @@ __global__ __launch_bounds__(kColThreads16, 3) void k_colsum16(EvictArgs a) {
     float ps[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int rh = 0; rh < RT / 16; ++rh) {
+      // a quarter of rows past the window, or none of which sees a key of the wave
+      if constexpr (!FULL)
+        if (t0 + 16 * rh >= a.W || (a.causal && jw > a.T - a.W + t0 + 16 * rh + 15)) continue;
       // this lane's rows of the quarter: t0 + 16 rh + 4 (lane / 16) + r
       const float4 nb4 = *(const float4*)&s_nb[buf][16 * rh + 4 * q4];
       const float4 il4 = *(const float4*)&s_il[buf][16 * rh + 4 * q4];
@@ -837,10 +847,13 @@ __global__ __launch_bounds__(kColThreads16, 3) void k_colsum16(EvictArgs a) {
   for (int it = 0; it < ntile; ++it) {
     const int buf = it & 1;
     if (it + 1 < ntile) fetch();
-    if (t0 + RT - 1 < a.W && (!a.causal || jw + 63 <= a.T - a.W + t0))
-      tile(std::true_type{}, buf);
-    else
-      tile(std::false_type{}, buf);
+    // keys past the prompt, or past what the tile's last row sees: the wave only helps stage the tile
+    if (jw < a.T && (!a.causal || jw <= a.T - a.W + t0 + RT - 1)) {
+      if (t0 + RT - 1 < a.W && (!a.causal || jw + 63 <= a.T - a.W + t0))
+        tile(std::true_type{}, buf);
+      else
+        tile(std::false_type{}, buf);
+    }
     if (it + 1 < ntile) stash(buf ^ 1);
     t0 = t0 + RT == t_end ? t_start : t0 + RT;
     __syncthreads();
