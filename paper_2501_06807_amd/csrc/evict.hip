@@ -23,8 +23,8 @@
 //     exponents of the terms near the max lie in (-2, 5] (16-bit inputs; nearly always below 4), so
 //     their rounding, and that of c (proportional to |c * (s - m)|), stay smallest on the terms that
 //     carry the sums.
-// The top-k is a 4-pass, 8-bit LDS radix select on the fp32 score bits followed by an ordered
-// block compaction, each thread's run of scores held in registers up to 32K older tokens; the
+// The top-k is an 8-bit LDS radix select on the fp32 score bits followed by an ordered block
+// compaction, each thread's run of scores held in registers up to 32K older tokens; the
 // gather copies kept rows with 16-byte lanes (all layers, or those whose representatives are not
 // built in the same pass).
 #include "evict.h"
@@ -867,39 +867,49 @@ __global__ __launch_bounds__(kColThreads16, 3) void k_colsum16(EvictArgs a) {
   }
 }
 
-// Exclusive prefix sum over the 1024 threads of a workgroup.
-__device__ int block_excl_scan(int v, int* wsum) {
+// ---------------------------------------------------------------------------------------------
+// Top-k: the n_sel best-scored older tokens of an owner head, in ascending order, by one workgroup.
+// Scores are non-negative, so their bits order like their values. A radix select finds the threshold: it
+// starts at the highest bit in which the largest and the smallest score differ (below it the bins spread,
+// above it every score would count into one bin), and ends as soon as a bin is taken whole, which for
+// distinct scores happens after about two digits. Then an ordered compaction: the scores above the
+// threshold bin, and as many of the bin (all, or of equal scores the lowest positions) as are wanted.
+constexpr int kHistCopies = 4;  // histograms of a workgroup, one per wave modulo this
+
+template <int NT>
+struct TopkLds {
+  uint32_t hist[kHistCopies][256];
+  uint32_t tot[256];
+  uint32_t red[2][NT / kWave];
+  uint32_t prefix;
+  int rem, done;
+  uint32_t wsum[NT / kWave], wbin[NT / kWave];
+};
+
+// Exclusive prefix sum over the NT threads of a workgroup.
+template <int NT>
+__device__ uint32_t block_excl_scan(uint32_t v, uint32_t* wsum) {
+  constexpr int NW = NT / kWave;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int x = v;
+  uint32_t x = v;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o);
+    const uint32_t y = __shfl_up(x, o);
     if (lane >= o) x += y;
   }
   if (lane == 63) wsum[w] = x;
   __syncthreads();
-  if (w == 0) {
-    int s = lane < 16 ? wsum[lane] : 0;
+  uint32_t before = 0;
 #pragma unroll
-    for (int o = 1; o < 16; o <<= 1) {
-      const int y = __shfl_up(s, o);
-      if (lane >= o) s += y;
-    }
-    if (lane < 16) wsum[lane] = s;
-  }
-  __syncthreads();
-  const int res = (w > 0 ? wsum[w - 1] : 0) + x - v;
-  __syncthreads();
-  return res;
+  for (int i = 0; i < NW; ++i) before += i < w ? wsum[i] : 0;
+  return before + x - v;
 }
 
-constexpr int kTopkThreads = 1024;
-
-// The radix digit (bins in descending order) at which the running count of tot[] reaches rem, by
-// the 64 lanes of wave 0 (four bins each, a wave prefix sum): writes prefix | digit << shift to
-// *s_prefix and rem minus the count of the higher bins to *s_rem. Requires sum(tot) >= rem >= 1.
+// The digit (bins in descending order) at which the running count of tot[] reaches rem, by the 64 lanes of
+// wave 0 (four bins each, a wave prefix sum): writes prefix | digit << shift, rem minus the count of the
+// higher bins, and whether the bin is taken whole. Requires sum(tot) >= rem >= 1.
 __device__ __forceinline__ void pick_digit(const uint32_t* tot, int rem, uint32_t prefix, int shift,
-                                           uint32_t* s_prefix, int* s_rem) {
+                                           uint32_t* s_prefix, int* s_rem, int* s_done) {
   const int lane = threadIdx.x & 63;
   uint32_t c[4], sum = 0;
 #pragma unroll
@@ -920,98 +930,83 @@ __device__ __forceinline__ void pick_digit(const uint32_t* tot, int rem, uint32_
     if (cum < r && r <= cum + c[u]) {
       *s_prefix = prefix | ((uint32_t)(255 - 4 * lane - u) << shift);
       *s_rem = (int)(r - cum);
+      *s_done = r == cum + c[u];
     }
     cum += c[u];
   }
 }
 
-__global__ __launch_bounds__(kTopkThreads) void k_topk(EvictArgs a) {
-  __shared__ uint32_t hist[kTopkThreads / 64][256];
-  __shared__ uint32_t tot[256];
-  __shared__ uint32_t s_prefix;
-  __shared__ int s_rem;
-  __shared__ int wsum[16];
-
-  const int ou = blockIdx.x;  // (owner index * B + b) * Hkv + h
-  const int l = a.own.local(ou / (a.B * a.Hkv));
-  const size_t unit = (size_t)l * a.B * a.Hkv + ou % (a.B * a.Hkv);
-  const int tid = threadIdx.x, w = tid >> 6;
-  const int loc = min(a.local_keep, a.keep);
-  const int n_old = a.T - loc, n_sel = a.keep - loc;
-  const uint32_t* key = (const uint32_t*)(a.score + (size_t)unit * a.T);
-  int32_t* out = a.kept + (size_t)unit * a.keep;
-
-  // radix select: the n_sel-th largest key (non-negative floats order like their bits)
-  uint32_t prefix = 0, mask = 0;
-  int rem = n_sel;
-  if (n_sel > 0) {
-    for (int shift = 24; shift >= 0; shift -= 8) {
-      for (int i = tid; i < (kTopkThreads / 64) * 256; i += kTopkThreads) hist[i / 256][i % 256] = 0;
-      __syncthreads();
-      for (int j = tid; j < n_old; j += kTopkThreads) {
-        const uint32_t u = key[j];
-        if ((u & mask) == prefix) atomicAdd(&hist[w][(u >> shift) & 255u], 1u);
-      }
-      __syncthreads();
-      if (tid < 256) {
-        uint32_t s = 0;
-        for (int i = 0; i < kTopkThreads / 64; ++i) s += hist[i][tid];
-        tot[tid] = s;
-      }
-      __syncthreads();
-      if (tid < 64) pick_digit(tot, rem, prefix, shift, &s_prefix, &s_rem);
-      __syncthreads();
-      prefix = s_prefix;
-      rem = s_rem;
-      mask |= 255u << shift;
-      __syncthreads();
-    }
+// The threshold bin of the rem best of a head's scores: scores with (u & mask) > prefix are in, and `rem`
+// of those with (u & mask) == prefix. each(f) calls f(u) for every score of the calling thread.
+template <int NT, class Each>
+__device__ void radix_threshold(TopkLds<NT>& s, Each each, int& rem, uint32_t& prefix, uint32_t& mask) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  uint32_t hi = 0u, lo = ~0u;
+  each([&](uint32_t u) {
+    hi = max(hi, u);
+    lo = min(lo, u);
+  });
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, o));
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, o));
   }
-  // ordered compaction: keys above the threshold, then the lowest-index ties up to `rem`
-  const int chk = (n_old + kTopkThreads - 1) / kTopkThreads;
-  const int j0 = min(n_old, tid * chk), j1 = min(n_old, j0 + chk);
-  int gt = 0, eq = 0;
-  if (n_sel > 0)
-    for (int j = j0; j < j1; ++j) {
-      const uint32_t u = key[j];
-      gt += u > prefix;
-      eq += u == prefix;
-    }
-  const int eq_before = block_excl_scan(eq, wsum);
-  const int take = n_sel > 0 ? max(0, min(eq, rem - eq_before)) : 0;
-  int off = block_excl_scan(gt + take, wsum);
-  if (n_sel > 0) {
-    int taken = 0;
-    for (int j = j0; j < j1; ++j) {
-      const uint32_t u = key[j];
-      if (u > prefix || (u == prefix && taken < take)) {
-        taken += u == prefix;
-        out[off++] = j;
-      }
-    }
+  if (lane == 0) {
+    s.red[0][w] = hi;
+    s.red[1][w] = lo;
   }
-  for (int i = tid; i < loc; i += kTopkThreads) out[n_sel + i] = n_old + i;
+  for (int i = tid; i < kHistCopies * 256; i += NT) s.hist[i / 256][i % 256] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NT / kWave; ++i) {
+    hi = max(hi, s.red[0][i]);
+    lo = min(lo, s.red[1][i]);
+  }
+  int top = hi == lo ? 0 : 32 - __clz((int)(hi ^ lo));  // bits still undecided
+  mask = top >= 32 ? 0u : ~0u << top;
+  prefix = hi & mask;
+  while (top > 0) {
+    const int shift = max(0, top - 8);
+    each([&](uint32_t u) {
+      if ((u & mask) == prefix) atomicAdd(&s.hist[w % kHistCopies][(u >> shift) & 255u & ~(~0u << (top - shift))], 1u);
+    });
+    __syncthreads();
+    if (tid < 256) {
+      uint32_t sum = 0;
+#pragma unroll
+      for (int i = 0; i < kHistCopies; ++i) {
+        sum += s.hist[i][tid];
+        s.hist[i][tid] = 0;
+      }
+      s.tot[tid] = sum;
+    }
+    __syncthreads();
+    if (tid < 64) pick_digit(s.tot, rem, prefix, shift, &s.prefix, &s.rem, &s.done);
+    __syncthreads();
+    prefix = s.prefix;
+    rem = s.rem;
+    top = s.done ? 0 : shift;
+    mask = ~0u << shift;
+  }
 }
 
-// The same selection with each thread's run of KPT scores held in registers from one read on:
-// the radix passes and the compaction read registers, not the score buffer (which otherwise is
-// re-read from memory by every pass once the heads in flight outgrow the L2).
-template <int KPT>
-__global__ __launch_bounds__(kTopkThreads) void k_topk_reg(EvictArgs a) {
-  __shared__ uint32_t hist[kTopkThreads / 64][256];
-  __shared__ uint32_t tot[256];
-  __shared__ uint32_t s_prefix;
-  __shared__ int s_rem;
-  __shared__ int wsum[16];
-
+// Each thread holds a run of KPT scores in registers from one read on. NT follows the prompt (launch_topk):
+// a thread per 4 to 32 scores, and no more threads than scores, which is what short prompts of many heads
+// need. 4352 heads of 992 older tokens: 76 us with 1024 threads and four full digits, 17 us so; 32
+// heads of 7145: 13.5 and 12.5 us.
+template <int NT, int KPT>
+__global__ __launch_bounds__(NT) void k_topk_reg(EvictArgs a) {
+  __shared__ TopkLds<NT> s;
   const int ou = blockIdx.x;  // (owner index * B + b) * Hkv + h
   const int l = a.own.local(ou / (a.B * a.Hkv));
   const size_t unit = (size_t)l * a.B * a.Hkv + ou % (a.B * a.Hkv);
-  const int tid = threadIdx.x, w = tid >> 6;
+  const int tid = threadIdx.x;
   const int loc = min(a.local_keep, a.keep);
   const int n_old = a.T - loc, n_sel = a.keep - loc;
   const uint32_t* key = (const uint32_t*)(a.score + (size_t)unit * a.T);
   int32_t* out = a.kept + (size_t)unit * a.keep;
+  for (int i = tid; i < loc; i += NT) out[n_sel + i] = n_old + i;
+  if (n_sel <= 0) return;
 
   // this thread's run [j0, j0 + nv) of the older tokens' scores
   const int j0 = tid * KPT;
@@ -1030,55 +1025,134 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk_reg(EvictArgs a) {
 #pragma unroll
     for (int i = 0; i < KPT; ++i) kv[i] = i < nv ? key[j0 + i] : 0u;
   }
-
-  // radix select: the n_sel-th largest key (non-negative floats order like their bits)
-  uint32_t prefix = 0, mask = 0;
   int rem = n_sel;
-  if (n_sel > 0) {
-    for (int shift = 24; shift >= 0; shift -= 8) {
-      for (int i = tid; i < (kTopkThreads / 64) * 256; i += kTopkThreads) hist[i / 256][i % 256] = 0;
-      __syncthreads();
+  uint32_t prefix, mask;
+  radix_threshold<NT>(s,
+                      [&](auto f) {
 #pragma unroll
-      for (int i = 0; i < KPT; ++i)
-        if (i < nv && (kv[i] & mask) == prefix) atomicAdd(&hist[w][(kv[i] >> shift) & 255u], 1u);
-      __syncthreads();
-      if (tid < 256) {
-        uint32_t s = 0;
-        for (int i = 0; i < kTopkThreads / 64; ++i) s += hist[i][tid];
-        tot[tid] = s;
-      }
-      __syncthreads();
-      if (tid < 64) pick_digit(tot, rem, prefix, shift, &s_prefix, &s_rem);
-      __syncthreads();
-      prefix = s_prefix;
-      rem = s_rem;
-      mask |= 255u << shift;
-      __syncthreads();
-    }
-  }
-  // ordered compaction: keys above the threshold, then the lowest-index ties up to `rem`
-  int gt = 0, eq = 0;
-  if (n_sel > 0) {
+                        for (int i = 0; i < KPT; ++i)
+                          if (i < nv) f(kv[i]);
+                      },
+                      rem, prefix, mask);
+  static_assert(NT * KPT <= 1 << 15, "counts fit 16 bits");
+  uint32_t cnt = 0;  // scores of the bin, then (upper half) scores above it
 #pragma unroll
-    for (int i = 0; i < KPT; ++i) {
-      gt += i < nv && kv[i] > prefix;
-      eq += i < nv && kv[i] == prefix;
-    }
-  }
-  const int eq_before = block_excl_scan(eq, wsum);
-  const int take = n_sel > 0 ? max(0, min(eq, rem - eq_before)) : 0;
-  int off = block_excl_scan(gt + take, wsum);
-  if (n_sel > 0) {
-    int taken = 0;
+  for (int i = 0; i < KPT; ++i)
+    if (i < nv) cnt += (kv[i] & mask) > prefix ? 1u << 16 : (kv[i] & mask) == prefix;
+  const uint32_t before = block_excl_scan<NT>(cnt, s.wsum);
+  int eq = (int)(before & 0xFFFFu), off = (int)(before >> 16) + min(eq, rem);
 #pragma unroll
-    for (int i = 0; i < KPT; ++i) {
-      if (i < nv && (kv[i] > prefix || (kv[i] == prefix && taken < take))) {
-        taken += kv[i] == prefix;
-        out[off++] = j0 + i;
-      }
-    }
+  for (int i = 0; i < KPT; ++i) {
+    if (i >= nv) break;
+    const uint32_t u = kv[i] & mask;
+    if (u > prefix || (u == prefix && eq < rem)) out[off++] = j0 + i;
+    eq += u == prefix;
   }
-  for (int i = tid; i < loc; i += kTopkThreads) out[n_sel + i] = n_old + i;
+}
+
+// Longer prompts: each wave streams a contiguous share of the scores, 256 at a time (four per lane), and
+// places its own by wave prefix sums. 8 heads of 131040 older tokens: 277 us with one score per thread and
+// step and four full digits, 119 us so.
+constexpr int kTopkThreads = 1024;
+
+__global__ __launch_bounds__(kTopkThreads) void k_topk(EvictArgs a) {
+  constexpr int NT = kTopkThreads, NW = NT / kWave, STEP = 4 * kWave;
+  __shared__ TopkLds<NT> s;
+  const int ou = blockIdx.x;  // (owner index * B + b) * Hkv + h
+  const int l = a.own.local(ou / (a.B * a.Hkv));
+  const size_t unit = (size_t)l * a.B * a.Hkv + ou % (a.B * a.Hkv);
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int loc = min(a.local_keep, a.keep);
+  const int n_old = a.T - loc, n_sel = a.keep - loc;
+  const uint32_t* key = (const uint32_t*)(a.score + (size_t)unit * a.T);
+  int32_t* out = a.kept + (size_t)unit * a.keep;
+  for (int i = tid; i < loc; i += NT) out[n_sel + i] = n_old + i;
+  if (n_sel <= 0) return;
+
+  const int share = (n_old + NW * STEP - 1) / (NW * STEP) * STEP;
+  const int lo = min(n_old, w * share), hi = min(n_old, lo + share);  // this wave's scores
+  const bool wide = ((uintptr_t)key & 15) == 0;
+  // scores j .. j + 3 (those below hi)
+  auto four = [&](int j, uint32_t (&v)[4]) {
+    if (wide && j + 4 <= hi) {
+      const uint4 q = *(const uint4*)(key + j);
+      v[0] = q.x;
+      v[1] = q.y;
+      v[2] = q.z;
+      v[3] = q.w;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = j + i < hi ? key[j + i] : 0u;
+    }
+  };
+  int rem = n_sel;
+  uint32_t prefix, mask;
+  radix_threshold<NT>(s,
+                      [&](auto f) {
+#pragma unroll 4
+                        for (int b = lo; b < hi; b += STEP) {
+                          const int j = b + 4 * lane;
+                          uint32_t v[4];
+                          four(j, v);
+#pragma unroll
+                          for (int i = 0; i < 4; ++i)
+                            if (j + i < hi) f(v[i]);
+                        }
+                      },
+                      rem, prefix, mask);
+  auto tally = [&](int j, const uint32_t (&v)[4]) {
+    uint32_t c = 0;  // scores of the bin, then (upper half) scores above it: at most 256 in a step
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (j + i < hi) c += (v[i] & mask) > prefix ? 1u << 16 : (v[i] & mask) == prefix;
+    return c;
+  };
+  uint32_t above = 0, bin = 0;
+#pragma unroll 4
+  for (int b = lo; b < hi; b += STEP) {
+    uint32_t v[4];
+    four(b + 4 * lane, v);
+    const uint32_t c = tally(b + 4 * lane, v);
+    above += c >> 16;
+    bin += c & 0xFFFFu;
+  }
+  above = wave_sum(above);
+  bin = wave_sum(bin);
+  if (lane == 0) {
+    s.wsum[w] = above;
+    s.wbin[w] = bin;
+  }
+  __syncthreads();
+  above = bin = 0;  // of the scores before this wave's, then before its next step's
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    above += i < w ? s.wsum[i] : 0;
+    bin += i < w ? s.wbin[i] : 0;
+  }
+#pragma unroll 4
+  for (int b = lo; b < hi; b += STEP) {
+    const int j = b + 4 * lane;
+    uint32_t v[4];
+    four(j, v);
+    const uint32_t c = tally(j, v);
+    uint32_t x = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(x, o);
+      if (lane >= o) x += y;
+    }
+    int eq = (int)(bin + ((x - c) & 0xFFFFu)), off = (int)(above + ((x - c) >> 16)) + min(eq, rem);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (j + i >= hi) break;
+      const uint32_t u = v[i] & mask;
+      if (u > prefix || (u == prefix && eq < rem)) out[off++] = j + i;
+      eq += u == prefix;
+    }
+    const uint32_t all = __shfl(x, 63);
+    above += all >> 16;
+    bin += all & 0xFFFFu;
+  }
 }
 
 template <int RB>
@@ -1178,20 +1252,28 @@ hipError_t launch_colsum(const EvictArgs& a, int dtype, int D, hipStream_t st) {
   return launch_pass_any(a, dtype, D, false, st);
 }
 
+template <int NT, int KPT>
+static void launch_topk_reg(const EvictArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL((k_topk_reg<NT, KPT>), dim3(a.own.n * a.B * a.Hkv), dim3(NT), 0, st, a);
+}
+
 hipError_t launch_topk(const EvictArgs& a, hipStream_t st) {
   // a run of up to 32 scores per thread stays in registers; longer prompts stream the scores
-  const dim3 grid(a.own.n * a.B * a.Hkv), block(kTopkThreads);
   const int n_old = a.T - min(a.local_keep, a.keep);
-  if (n_old <= 4 * kTopkThreads)
-    hipLaunchKernelGGL(k_topk_reg<4>, grid, block, 0, st, a);
-  else if (n_old <= 8 * kTopkThreads)
-    hipLaunchKernelGGL(k_topk_reg<8>, grid, block, 0, st, a);
-  else if (n_old <= 16 * kTopkThreads)
-    hipLaunchKernelGGL(k_topk_reg<16>, grid, block, 0, st, a);
-  else if (n_old <= 32 * kTopkThreads)
-    hipLaunchKernelGGL(k_topk_reg<32>, grid, block, 0, st, a);
+  if (n_old <= 1024)
+    launch_topk_reg<256, 4>(a, st);
+  else if (n_old <= 2048)
+    launch_topk_reg<512, 4>(a, st);
+  else if (n_old <= 4096)
+    launch_topk_reg<1024, 4>(a, st);
+  else if (n_old <= 8192)
+    launch_topk_reg<1024, 8>(a, st);
+  else if (n_old <= 16384)
+    launch_topk_reg<1024, 16>(a, st);
+  else if (n_old <= 32768)
+    launch_topk_reg<1024, 32>(a, st);
   else
-    hipLaunchKernelGGL(k_topk, grid, block, 0, st, a);
+    hipLaunchKernelGGL(k_topk, dim3(a.own.n * a.B * a.Hkv), dim3(kTopkThreads), 0, st, a);
   return hipGetLastError();
 }
 
