@@ -228,6 +228,26 @@ __device__ __forceinline__ double dpp_f64(double x) {
   return __hiloint2double(hi, lo);
 }
 
+// op(x, x of lane ^ O) in every lane, for O = 8, 16 or 32 and a commutative op: a row rotation within 16
+// lanes, or the lane swaps of gfx950 (v_permlane16_swap / v_permlane32_swap give both partners' values in a
+// register pair), all VALU; a __shfl_xor goes through LDS.
+template <int O, class Op>
+__device__ __forceinline__ float xor_combine(float x, Op op) {
+  static_assert(O == 8 || O == 16 || O == 32, "lane distance");
+  if constexpr (O == 8) {
+    return op(x, dpp_f32<0x128>(x));
+  } else {
+    const unsigned u = __float_as_uint(x);
+    if constexpr (O == 16) {
+      const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+      return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    } else {
+      const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+      return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    }
+  }
+}
+
 // Sum over aligned groups of N consecutive lanes; every lane of a group receives its group's sum.
 // Each step adds a lane permutation that pairs partial sums, so after log2(N) steps every lane
 // has seen all N inputs (rotations by 8, 4, 2, 1 within 16 lanes; mirror + quad swaps within 8).
