@@ -113,7 +113,7 @@ DecodeWs decode_ws(const mpc_dims* d, bool per_q_head) {
   const int heads = per_q_head ? d->n_q_heads : d->n_kv_heads;
   const int units = d->n_layers * d->batch * heads;
   const int G = d->n_q_heads / heads;
-  const mpc::DecodePlan p = mpc::decode_plan(units, 1 << 30, d->head_dim, elt_size(d->dtype));
+  const mpc::DecodePlan p = mpc::decode_plan(units, 1 << 30, d->head_dim, elt_size(d->dtype), G);
   DecodeWs w{0, 0};
   if (p.splits <= 1) return w;
   w.cnt = align256((size_t)units * p.splits * G * (d->head_dim + 2) * sizeof(float));
@@ -454,7 +454,7 @@ mpc_status prepare_decode(const mpc_dims* dims, int32_t Ts, int32_t n_tail, int3
   if (n_list > 1024) return fail(MPC_EUNSUPPORTED, "k_clusters plus tail clusters above 1024");
   if ((int64_t)n_list * cluster_size >= ((int64_t)1 << 30)) return fail(MPC_EUNSUPPORTED, "too many tokens");
   const int units = dims->n_layers * dims->batch * sel_heads;
-  *plan = mpc::decode_plan(units, n_list * cluster_size, dims->head_dim, elt_size(dims->dtype));
+  *plan = mpc::decode_plan(units, n_list * cluster_size, dims->head_dim, elt_size(dims->dtype), G);
   mpc::DecodeArgs a{};
   a.q = q;
   a.k = k_cache;
@@ -518,7 +518,7 @@ mpc_status mpc_sparse_decode_attn(const mpc_dims* dims, int32_t Ts, int32_t n_ta
                                 sm_scale, out, lse, &a, &plan, &units, &G);
   if (s != MPC_OK) return s;
   const size_t need = decode_ws_bytes(dims);
-  if (plan.splits > 1 && (!ws || ws_bytes < need))
+  if (plan.most > 1 && (!ws || ws_bytes < need))
     return fail(MPC_EWORKSPACE, "sparse decode attention needs %zu workspace bytes", need);
   if (plan.splits > 1) {
     a.part = (float*)ws;

@@ -50,20 +50,34 @@ hipError_t launch_dt(const DecodeArgs& a, int D, int G, int units, const DecodeP
 
 }  // namespace
 
-DecodePlan decode_plan(int units, int n_slot, int D, int elt) {
+DecodePlan decode_plan(int units, int n_slot, int D, int elt, int G) {
   // One 8-wave workgroup per unit when there are at least as many units as CUs; otherwise the
-  // token list of each unit is split over several workgroups (about two per CU).
+  // token list of each unit may be split over several workgroups (at most about two per CU).
   DecodePlan p;
   p.waves = 8;
-  p.splits = 1;
+  p.splits = p.most = 1;
   if (units < kNumCU) {
     const int lpr = D * elt / 16;
     const int rows_per_pass = p.waves * (kWave / lpr);
     int max_splits = n_slot / rows_per_pass;
     if (max_splits < 1) max_splits = 1;
-    p.splits = (2 * kNumCU + units - 1) / units;
-    if (p.splits > max_splits) p.splits = max_splits;
-    if (p.splits > kMaxSplits) p.splits = kMaxSplits;
+    p.most = (2 * kNumCU + units - 1) / units;
+    if (p.most > max_splits) p.most = max_splits;
+    if (p.most > kMaxSplits) p.most = kMaxSplits;
+    // A split pays for its partial's stores, the arrival and the merge (three memory round trips, about
+    // 3 us), so each gets at least 64 KiB of K rows, less where a row serves more query heads than two
+    // (its arithmetic then weighs more). Measured, us per launch, splits in parentheses:
+    //   32 units of 384 rows of 256 B        8.9 (12)   6.2 (3)   5.7 (1)
+    //   32 units of 1632 rows of 256 B      10.5 (16)   9.1 (6)  11.2 (3)
+    //   64 units of 384 rows of 512 B        8.3 (8)    7.8 (3)  10.5 (1)
+    //   144 units of 128 rows of 128 B       7.0 (4)    4.4 (1)
+    //   8 units of 640 rows of 256 B, G = 4 10.1 (16)   9.3 (5)  11.5 (2)  12.1 (1)
+    //   8 units of 960 rows of 256 B, G = 8 16.2 (16)  17.2 (7)  20.6 (3)  34.5 (1)
+    int least = (64 << 10) / (D * elt);
+    if (G > 2) least /= G / 2;
+    p.splits = n_slot / least;
+    if (p.splits > p.most) p.splits = p.most;
+    if (p.splits < 1) p.splits = 1;
   }
   return p;
 }
