@@ -552,10 +552,12 @@ mpc_status mpc_decode_step(const mpc_dims* dims, int32_t Ts, int32_t n_tail, con
   hipStream_t st = (hipStream_t)stream;
   clear_stale_error();
   const mpc::FusedPlan fp = mpc::fused_plan(sa, dims->head_dim, plan.splits);
-  if ((!fp.self && (per_q_head || plan.splits > 1)) || !mpc::fused_fits(fp, dims->head_dim, G)) {
-    // two kernels in sequence
+  if (plan.splits > 1) {
     da.part = (float*)((char*)ws + lay.part);
     da.cnt = (int*)((char*)ws + lay.part + decode_ws(dims, per_q_head).cnt);
+  }
+  if ((!fp.self && (per_q_head || plan.splits > 1)) || !mpc::fused_fits(fp, dims->head_dim, G)) {
+    // two kernels in sequence
     if (sa.own.n > 0 &&
         (s = launched(mpc::launch_select(sa, dims->dtype, dims->head_dim, st), "select")) != MPC_OK)
       return s;

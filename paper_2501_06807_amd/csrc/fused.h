@@ -30,6 +30,11 @@ struct FusedPlan {
 FusedPlan fused_plan(const SelectArgs& s, int D, int splits);
 // Whether the selection's LDS and the attention's fit one workgroup's LDS together.
 bool fused_fits(const FusedPlan& p, int D, int G);
+constexpr int kFusedWaves = 8;  // waves per workgroup
+
+hipError_t launch_decode_step_fp32(const FusedArgs& f, const FusedPlan& p, int D, int G, hipStream_t st);
+hipError_t launch_decode_step_fp16(const FusedArgs& f, const FusedPlan& p, int D, int G, hipStream_t st);
+hipError_t launch_decode_step_bf16(const FusedArgs& f, const FusedPlan& p, int D, int G, hipStream_t st);
 hipError_t launch_decode_step(const FusedArgs& f, const FusedPlan& p, int dtype, int D, int G,
                               hipStream_t st);
 

@@ -393,7 +393,7 @@ __device__ __forceinline__ void emit_selection(const SelectArgs& a, const int* t
 // Writes the level-2 result of a workgroup that attends one layer itself: entry top[j] (j <
 // k_clusters) goes to its ascending position of `pick` (LDS, read by the same workgroup's attention)
 // and of layer l's row of the selection output (layer l uses the selection of its owner head, which
-// the workgroup computed). Threads t0, t0 + nt, ...
+// the workgroup computed; l < 0: another workgroup writes that row). Threads t0, t0 + nt, ...
 __device__ __forceinline__ void emit_pick(const SelectArgs& a, const int* top, const int* cand, const double* s2,
                                           int l, int b, int h, int32_t* pick, int t0, int nt) {
   const size_t o0 = (((size_t)l * a.B + b) * a.Hsel + h) * a.k_clusters;
@@ -401,6 +401,7 @@ __device__ __forceinline__ void emit_pick(const SelectArgs& a, const int* top, c
     const int i = top[j], p = ascending_pos(top, a.k_clusters, j);
     const int c = cand[i];
     pick[p] = c;
+    if (l < 0) continue;
     a.sel[o0 + p] = c;
     if (a.sel_score) a.sel_score[o0 + p] = (float)s2[i];
   }
@@ -457,6 +458,7 @@ __device__ __forceinline__ void emit_entry(const SelectArgs& a, int c, float sc,
                                            int h, int32_t* pick, int pick_layer) {
   if (pick) {
     pick[p] = c;
+    if (pick_layer < 0) return;
     const size_t o = (((size_t)pick_layer * a.B + b) * a.Hsel + h) * a.k_clusters + p;
     a.sel[o] = c;
     if (a.sel_score) a.sel_score[o] = sc;
@@ -646,8 +648,8 @@ __device__ void select_block_reg(const SelectArgs& a, typename SC::Tile& tile, c
 // bound scores (two-row representatives), else dot-product scores. QREG: keep the summed query in
 // registers (faster) rather than reading it from LDS at every row (fewer registers). GMAX: the
 // unit's score is the maximum of its q-heads' similarities, not their sum. pick: if not null, the
-// selection goes to this LDS array and to layer pick_layer's output row only (emit_pick), instead
-// of every layer of the call that shares it.
+// selection goes to this LDS array and to layer pick_layer's output row only (emit_pick; to none when
+// negative), instead of every layer of the call that shares it.
 template <class DT, int D, int NW, bool COH, int PASS = 2, bool MP = false, bool QREG = true, bool GMAX = false>
 __device__ void select_block(const SelectArgs& a, int ou, unsigned char* smem, int32_t* pick = nullptr,
                              int pick_layer = -1) {
