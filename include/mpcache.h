@@ -242,9 +242,9 @@ mpc_status mpc_sparse_decode_attn(const mpc_dims* dims, int32_t Ts, int32_t n_ta
  * reached (no such case is known: it would take a selection that never gets published), the unit
  * sets bit 0 of the error word and writes NaN to its out and lse rows instead of attending; the
  * call still returns MPC_OK, since the status covers only validation and launch.
- * Blocks whose attention is split over several workgroups per unit, whose selection and attention
- * together need more LDS than one workgroup has, or that select per q-head (MPC_GROUP_HEAD) run the
- * two kernels one after the other instead (same results). */
+ * Blocks of more attention workgroups than the chip holds at once, or of short lists on more of them than
+ * compute units, and blocks whose selection and attention together need more LDS than one workgroup has, run
+ * the two kernels one after the other instead (same results). */
 mpc_status mpc_decode_step(const mpc_dims* dims, int32_t Ts, int32_t n_tail, const mpc_select_cfg* cfg,
                            const void* q, const float* cent, const float* scent,
                            const void* k_cache, const void* v_cache, float sm_scale, int32_t* sel,

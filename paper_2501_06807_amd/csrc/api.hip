@@ -113,7 +113,7 @@ DecodeWs decode_ws(const mpc_dims* d, bool per_q_head) {
   const int heads = per_q_head ? d->n_q_heads : d->n_kv_heads;
   const int units = d->n_layers * d->batch * heads;
   const int G = d->n_q_heads / heads;
-  const mpc::DecodePlan p = mpc::decode_plan(units, 1 << 30, d->head_dim, elt_size(d->dtype), G);
+  const mpc::DecodePlan p = mpc::decode_plan(units, 1 << 30, 1, d->head_dim, elt_size(d->dtype), G);
   DecodeWs w{0, 0};
   if (p.splits <= 1) return w;
   w.cnt = align256((size_t)units * p.splits * G * (d->head_dim + 2) * sizeof(float));
@@ -454,7 +454,7 @@ mpc_status prepare_decode(const mpc_dims* dims, int32_t Ts, int32_t n_tail, int3
   if (n_list > 1024) return fail(MPC_EUNSUPPORTED, "k_clusters plus tail clusters above 1024");
   if ((int64_t)n_list * cluster_size >= ((int64_t)1 << 30)) return fail(MPC_EUNSUPPORTED, "too many tokens");
   const int units = dims->n_layers * dims->batch * sel_heads;
-  *plan = mpc::decode_plan(units, n_list * cluster_size, dims->head_dim, elt_size(dims->dtype), G);
+  *plan = mpc::decode_plan(units, n_list * cluster_size, cluster_size, dims->head_dim, elt_size(dims->dtype), G);
   mpc::DecodeArgs a{};
   a.q = q;
   a.k = k_cache;
@@ -556,7 +556,14 @@ mpc_status mpc_decode_step(const mpc_dims* dims, int32_t Ts, int32_t n_tail, con
     da.part = (float*)((char*)ws + lay.part);
     da.cnt = (int*)((char*)ws + lay.part + decode_ws(dims, per_q_head).cnt);
   }
-  if ((!fp.self && (per_q_head || plan.splits > 1)) || !mpc::fused_fits(fp, dims->head_dim, G)) {
+  // The claiming launch trails the two kernels the more units wait for a selection and the shorter their lists
+  // are, since every unit's attention then stands behind one (us, one launch and two: 1024 units of 384 rows 50.7
+  // and 38.8, 288 of 128 13.2 and 10.5, 512 of 48 15.9 and 11.3). It keeps the blocks whose workgroups are all
+  // resident at once and have 64 KiB of K rows each, where it is within a tenth (512 of 384 rows 25.7 and 24.2, of 480
+  // 34.1 and 34.5) and a caller gets the one launch that this entry point is for.
+  const bool claim = !per_q_head && plan.splits == 1 && plan.waves > 1 && units <= 2 * mpc::kNumCU &&
+                     (int64_t)da.k_sel * da.s * dims->head_dim * elt_size(dims->dtype) >= (64 << 10);
+  if (!(fp.self || claim) || !mpc::fused_fits(fp, dims->head_dim, G)) {
     // two kernels in sequence
     if (sa.own.n > 0 &&
         (s = launched(mpc::launch_select(sa, dims->dtype, dims->head_dim, st), "select")) != MPC_OK)

@@ -35,12 +35,14 @@ struct DecodeArgs {
 constexpr long long kStreamKBytes = 256ll << 20;
 
 struct DecodePlan {
-  int waves;   // waves per workgroup
+  int waves;   // waves per unit
   int splits;  // workgroups per unit
   int most;    // splits the unit's rows allow; above one, the caller has to bring a workspace
 };
-// Plan of `units` work units of n_slot rows each, G query heads to a unit.
-DecodePlan decode_plan(int units, int n_slot, int D, int elt, int G);
+constexpr int kMaxWaveList = 64;  // list entries of a unit attended by one wave
+
+// Plan of `units` work units of n_slot rows each (clusters of s), G query heads to a unit.
+DecodePlan decode_plan(int units, int n_slot, int s, int D, int elt, int G);
 hipError_t launch_sparse_decode(const DecodeArgs& a, int dtype, int D, int G, int units, const DecodePlan& p,
                                 hipStream_t st);
 

@@ -20,9 +20,28 @@ __global__ __launch_bounds__(NW* kWave) void k_sparse_decode(DecodeArgs a) {
   dev::attend<DT, D, G, NW, U, false, STREAM_K>(a, blockIdx.x / a.splits, blockIdx.x % a.splits);
 }
 
+constexpr int kUnitWaves = 4;  // units (waves) per workgroup of the wave form
+
+template <class DT, int D, int G, int U, bool STREAM_K>
+__global__ __launch_bounds__(kUnitWaves* kWave) void k_sparse_decode_wave(DecodeArgs a, int units) {
+  __shared__ int32_t s_sel[kUnitWaves][kMaxWaveList];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int unit = blockIdx.x * kUnitWaves + w;
+  if (unit < units) dev::attend_wave<DT, D, G, U, STREAM_K>(a, unit, s_sel[w]);
+}
+
 template <class DT, int D, int G>
 hipError_t launch_dt_d_g(const DecodeArgs& a, int units, const DecodePlan& p, hipStream_t st) {
-  (void)p;
+  if constexpr (G <= 2) {
+    if (p.waves == 1) {
+      const dim3 grid((units + kUnitWaves - 1) / kUnitWaves), block(kUnitWaves * kWave);
+      if (a.stream_k)
+        hipLaunchKernelGGL((k_sparse_decode_wave<DT, D, G, 4, true>), grid, block, 0, st, a, units);
+      else
+        hipLaunchKernelGGL((k_sparse_decode_wave<DT, D, G, 4, false>), grid, block, 0, st, a, units);
+      return hipGetLastError();
+    }
+  }
   if (a.stream_k)
     hipLaunchKernelGGL((k_sparse_decode<DT, D, G, 8, 4, true>), dim3(units * a.splits), dim3(8 * kWave), 0, st, a);
   else
@@ -50,7 +69,7 @@ hipError_t launch_dt(const DecodeArgs& a, int D, int G, int units, const DecodeP
 
 }  // namespace
 
-DecodePlan decode_plan(int units, int n_slot, int D, int elt, int G) {
+DecodePlan decode_plan(int units, int n_slot, int s, int D, int elt, int G) {
   // One 8-wave workgroup per unit when there are at least as many units as CUs; otherwise the
   // token list of each unit may be split over several workgroups (at most about two per CU).
   DecodePlan p;
@@ -79,6 +98,13 @@ DecodePlan decode_plan(int units, int n_slot, int D, int elt, int G) {
     if (p.splits > p.most) p.splits = p.most;
     if (p.splits < 1) p.splits = 1;
   }
+  // Many units with short lists: a wave each. A workgroup's pass is 32 KiB of K rows (8 waves of 4 loads of
+  // 1 KiB); a list of at most half of that leaves half of its lanes without a row, beside its barrier and the
+  // merge of its waves. us per launch, workgroup and wave form: 8192 units of 48 rows of 256 B 54.7 and 35.9, of 64
+  // rows 54.7 and 45.7, of 96 66.1 and 67.5, of 128 83.3 and 88.5; 4096 of 64 27.4 and 23.1; 8192 of 48 rows of
+  // 128 B 46.6 and 19.8, of 128 53.6 and 43.1; 1024 of 48 rows of 256 B 9.3 and 9.3.
+  if (G <= 2 && p.splits == 1 && units >= 4 * kNumCU && n_slot * D * elt <= (16 << 10) && n_slot <= kMaxWaveList * s)
+    p.waves = 1;
   return p;
 }
 

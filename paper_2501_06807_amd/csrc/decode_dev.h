@@ -312,6 +312,162 @@ __device__ __forceinline__ void attend_unit(const DecodeArgs& a, int unit, int s
   finish_unit<DT, D, G, NW>(a, unit, split, q_row0, s_m, s_l, s_acc);
 }
 
+// Attention of a unit with a short list by one wave (s_sel: its own list of at most kMaxWaveList entries): the
+// lane layout and arithmetic of attend_unit, with no barrier and no merge through LDS.
+template <class DT, int D, int G, int U, bool STREAM_K>
+__device__ __forceinline__ void attend_wave(const DecodeArgs& a, int unit, int32_t* s_sel) {
+  constexpr int EPL = DT::kVec;
+  constexpr int LPR = D / EPL;
+  constexpr int RPW = kWave / LPR;
+  constexpr bool kDot2 = DT::kElt == 2;
+  constexpr float kSlack = 8.f;
+  constexpr int STEP = RPW * U;
+
+  const int lane = threadIdx.x % kWave, rg = lane / LPR, li = lane % LPR;
+  const size_t q_row0 = (size_t)(unit / a.Hkv) * a.Hq + (size_t)(unit % a.Hkv) * G;
+  uint4 qraw[G];
+  float qf[G][EPL];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    qraw[g] = ldg16((const char*)a.q + ((q_row0 + g) * D + li * EPL) * DT::kElt);
+    if constexpr (!kDot2) {
+      float t[EPL];
+      unpack<DT>(qraw[g], t);
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) qf[g][e] = t[e] * a.qscale;
+    }
+  }
+  const int n_list = a.k_sel + (a.n_tail + a.s - 1) / a.s;
+  if (lane < n_list) {
+    int c = a.C + (lane - a.k_sel);
+    if (lane < a.k_sel) {
+      c = a.sel[(size_t)unit * a.k_sel + lane];
+      if ((unsigned)c >= (unsigned)a.C) c = -1;
+    }
+    s_sel[lane] = c;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+
+  const int n_slot = n_list * a.s, rows_end = a.Ts + a.n_tail;
+  const char* kbase = (const char*)a.k + cache_offset<D, DT>(a, unit) + li * 16;
+  const char* vbase = (const char*)a.v + cache_offset<D, DT>(a, unit) + li * 16;
+  float m[G], l[G], acc[G][EPL];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    m[g] = -1e30f;
+    l[g] = 0.f;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
+  }
+  // slot cursors (cluster position, row), advanced by STEP slots without a division
+  int cpos[U], crow[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int sl = u * RPW + rg;
+    cpos[u] = sl / a.s;
+    crow[u] = sl % a.s;
+  }
+  const int step_pos = STEP / a.s, step_row = STEP % a.s;
+  for (int base = 0; base < n_slot; base += STEP) {
+    uint4 kr[U], vr[U];
+    bool ok[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = s_sel[min(cpos[u], n_list - 1)];
+      const int r = c * a.s + crow[u];
+      ok[u] = (base + u * RPW + rg < n_slot) & (c >= 0) & (r < rows_end);
+      const unsigned off = (unsigned)(ok[u] ? r : 0) * (unsigned)(D * DT::kElt);
+      kr[u] = kv_load<STREAM_K>(kbase + off);
+      vr[u] = kv_load<true>(vbase + off);
+      crow[u] += step_row;
+      cpos[u] += step_pos;
+      if (crow[u] >= a.s) {
+        crow[u] -= a.s;
+        ++cpos[u];
+      }
+    }
+    float sc[U][G];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float kf[EPL];
+      if constexpr (!kDot2) unpack<DT>(kr[u], kf);
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        float p = 0.f;
+        if constexpr (kDot2) {
+          p = dot2<DT>(qraw[g].x, kr[u].x, p);
+          p = dot2<DT>(qraw[g].y, kr[u].y, p);
+          p = dot2<DT>(qraw[g].z, kr[u].z, p);
+          p = dot2<DT>(qraw[g].w, kr[u].w, p);
+        } else {
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) p += qf[g][e] * kf[e];
+        }
+        p = group_sum<LPR>(p);
+        if constexpr (kDot2) p *= a.qscale;
+        sc[u][g] = ok[u] ? p : -INFINITY;
+      }
+    }
+    float mx[G];
+    bool up = false;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      mx[g] = m[g];
+#pragma unroll
+      for (int u = 0; u < U; ++u) mx[g] = fmaxf(mx[g], sc[u][g]);
+      up |= mx[g] > m[g] + kSlack;
+    }
+    if (__any(up)) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const float r = fast_exp2(m[g] - mx[g]);
+        l[g] *= r;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[g][e] *= r;
+        m[g] = mx[g];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float vf[EPL];
+      unpack<DT>(vr[u], vf);
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const float p = fast_exp2(sc[u][g] - m[g]);
+        l[g] += p;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[g][e] += p * vf[e];
+      }
+    }
+  }
+  // the row groups meet at the largest maximum
+  auto hi = [](float x, float y) { return fmaxf(x, y); };
+  auto add = [](float x, float y) { return x + y; };
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    float M = m[g];
+    if constexpr (LPR <= 8) M = xor_combine<8>(M, hi);
+    if constexpr (LPR <= 16) M = xor_combine<16>(M, hi);
+    M = xor_combine<32>(M, hi);
+    const float r = fast_exp2(m[g] - M);
+    auto meet = [&](float x) {
+      x *= r;
+      if constexpr (LPR <= 8) x = xor_combine<8>(x, add);
+      if constexpr (LPR <= 16) x = xor_combine<16>(x, add);
+      return xor_combine<32>(x, add);
+    };
+    const float L = meet(l[g]);
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) acc[g][e] = meet(acc[g][e]);
+    if (rg == 0) {
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) store_elt<DT>(a.out, (q_row0 + g) * D + li * EPL + e, acc[g][e] / L);
+      if (li == 0 && a.lse) a.lse[q_row0 + g] = (M + __log2f(L)) * 0.69314718055994531f;
+    }
+  }
+}
+
 // Groups of four query heads over 16-bit rows: the scores come from the matrix cores
 // (v_mfma_f32_16x16x32_{bf16,f16}: A = the group's four queries, each repeated on four rows,
 // B = 16 gathered key rows), so every lane receives the four head scores of one token with no

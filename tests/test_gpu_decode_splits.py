@@ -70,3 +70,23 @@ def test_splits_match_oracle(shape):
     torch.cuda.synchronize()
     assert torch.equal(sels[0], sels[1])
     assert torch.equal(outs[0].view(torch.uint8), outs[1].view(torch.uint8))
+
+
+# many units with lists of at most 16 KiB of K rows (a wave each), and the first ones past that rule: layers,
+# sequences, query heads, kv heads, head dim, type, tokens per cluster, clusters selected, tail rows
+WAVE_SHAPES = [
+    (32, 1, 32, 32, 128, "bf16", 4, 16, 0),   # 64 rows of 256 B, the longest list of rows
+    (32, 1, 32, 32, 128, "bf16", 4, 15, 3),   # with a tail in a cluster of its own
+    (32, 1, 32, 32, 128, "bf16", 1, 63, 1),   # 64 entries
+    (32, 1, 32, 32, 128, "bf16", 1, 64, 1),   # 65: a workgroup
+    (32, 1, 32, 32, 128, "bf16", 5, 13, 0),   # 65 rows: a workgroup
+    (32, 2, 16, 16, 64, "fp16", 7, 18, 0),    # 126 rows of 128 B, clusters that no load step divides
+    (32, 1, 64, 32, 64, "bf16", 16, 2, 0),    # two query heads a row
+    (33, 1, 32, 32, 128, "fp32", 3, 10, 2),   # 30 rows of 512 B and the tail, a last workgroup of fewer units
+    (32, 1, 64, 32, 128, "fp32", 32, 1, 0),
+]
+
+
+@pytest.mark.parametrize("shape", WAVE_SHAPES)
+def test_short_lists_match_oracle(shape):
+    test_splits_match_oracle(shape)
