@@ -79,27 +79,33 @@ mpc_status launched(hipError_t e, const char* what) {
 constexpr size_t kScratchBytes = (size_t)32 << 20;  // static array of mpc_static_evict_noalloc
 
 // Static eviction workspace: the (exponent offset, 1 / sum) pair of every window row, then fp32
-// token scores, whose place the row pass's partials take before (they are merged by the time the first
-// score is written). Splits are taken only as far as a block that fits the static array with one split
-// stays inside it: no block is refused for its splits, and both entry points split alike.
+// token scores, then the column pass's partials. The row pass's partials take the place of both before (they are
+// merged by the time the column pass starts). Splits are taken only as far as a block that fits the static array
+// without them stays inside it: no block is refused for its splits, and both entry points split alike.
 struct EvictWs {
-  size_t rowstat, score, total;
-  int splits;
+  size_t rowstat, score, col_part, total;
+  int splits, col_splits;
 };
 EvictWs evict_ws(const mpc_dims* d, int T, const mpc_evict_cfg* cfg) {
   const int W = cfg->window;
   EvictWs w;
   w.rowstat = 0;
   w.score = align256((size_t)d->n_layers * d->batch * d->n_q_heads * W * sizeof(double));
-  const size_t base = w.score + align256((size_t)d->n_layers * d->batch * d->n_kv_heads * T * sizeof(float));
+  w.col_part = w.score + align256((size_t)d->n_layers * d->batch * d->n_kv_heads * T * sizeof(float));
   const mpc::OwnerTable own = mpc::owner_table(d->layer0, d->n_layers, cfg->share_period, cfg->share_start);
-  const size_t heads = (size_t)own.n * d->batch * d->n_q_heads;
+  const size_t heads = (size_t)own.n * d->batch * d->n_q_heads, kv_heads = (size_t)own.n * d->batch * d->n_kv_heads;
   w.splits = own.n > 0 ? mpc::row_splits((int)heads, T, W, cfg->causal) : 1;
-  auto total = [&](int s) {
-    return s == 1 ? base : std::max(base, w.score + align256(heads * s * W * sizeof(double2)));
+  w.col_splits = own.n > 0 ? mpc::col_splits((int)kv_heads, T, W, d->n_q_heads / d->n_kv_heads) : 1;
+  auto total = [&]() {
+    const size_t rows = w.splits > 1 ? w.score + align256(heads * w.splits * W * sizeof(double2)) : 0;
+    const size_t cols = w.col_splits > 1 ? w.col_part + align256(kv_heads * w.col_splits * T * sizeof(double)) : 0;
+    return std::max(w.col_part, std::max(rows, cols));
   };
-  while (w.splits > 1 && base <= kScratchBytes && total(w.splits) > kScratchBytes) --w.splits;
-  w.total = total(w.splits);
+  if (w.col_part <= kScratchBytes) {
+    while (w.col_splits > 1 && total() > kScratchBytes) --w.col_splits;
+    while (w.splits > 1 && total() > kScratchBytes) --w.splits;
+  }
+  w.total = total();
   return w;
 }
 
@@ -223,6 +229,8 @@ mpc_status prepare_evict(const mpc_dims* dims, int32_t T, const mpc_evict_cfg* c
   a.row_lse = row_lse;
   a.part = (double2*)((char*)ws + lay.score);
   a.splits = lay.splits;
+  a.col_part = (double*)((char*)ws + lay.col_part);
+  a.col_splits = lay.col_splits;
   a.B = dims->batch;
   a.layer0 = dims->layer0;
   a.n_layers = dims->n_layers;

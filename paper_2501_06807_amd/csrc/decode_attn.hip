@@ -22,8 +22,11 @@ __global__ __launch_bounds__(NW* kWave) void k_sparse_decode(DecodeArgs a) {
 
 constexpr int kUnitWaves = 4;  // units (waves) per workgroup of the wave form
 
+// One query head over 16-bit rows fits 64 registers, so that 32 units run on a compute unit at once: 8192 units of 48
+// rows are then one round (36.2 us at 70 registers, 34.4 at 64).
+
 template <class DT, int D, int G, int U, bool STREAM_K>
-__global__ __launch_bounds__(kUnitWaves* kWave) void k_sparse_decode_wave(DecodeArgs a, int units) {
+__global__ __launch_bounds__(kUnitWaves* kWave, G == 1 && DT::kElt == 2 ? 8 : 1) void k_sparse_decode_wave(DecodeArgs a, int units) {
   __shared__ int32_t s_sel[kUnitWaves][kMaxWaveList];
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int unit = blockIdx.x * kUnitWaves + w;
@@ -100,8 +103,8 @@ DecodePlan decode_plan(int units, int n_slot, int s, int D, int elt, int G) {
   }
   // Many units with short lists: a wave each. A workgroup's pass is 32 KiB of K rows (8 waves of 4 loads of
   // 1 KiB); a list of at most half of that leaves half of its lanes without a row, beside its barrier and the
-  // merge of its waves. us per launch, workgroup and wave form: 8192 units of 48 rows of 256 B 54.7 and 35.9, of 64
-  // rows 54.7 and 45.7, of 96 66.1 and 67.5, of 128 83.3 and 88.5; 4096 of 64 27.4 and 23.1; 8192 of 48 rows of
+  // merge of its waves. us per launch, workgroup and wave form: 8192 units of 48 rows of 256 B 54.7 and 34.4, of 64
+  // rows 54.7 and 44.1, of 96 66.1 and 67.5, of 128 83.3 and 88.5; 4096 of 64 27.4 and 23.1; 8192 of 48 rows of
   // 128 B 46.6 and 19.8, of 128 53.6 and 43.1; 1024 of 48 rows of 256 B 9.3 and 9.3.
   if (G <= 2 && p.splits == 1 && units >= 4 * kNumCU && n_slot * D * elt <= (16 << 10) && n_slot <= kMaxWaveList * s)
     p.waves = 1;

@@ -22,6 +22,8 @@ struct EvictArgs {
   float* row_lse;      // [L][B][Hq][W] natural log-sum-exp, optional
   double2* part;       // row pass partials [owner heads][splits][W]: (sum, offset); unused with one split
   int splits;          // workgroups that share a row block's keys
+  double* col_part;    // column pass partials [owner heads][col_splits][T]; unused with one split
+  int col_splits;      // workgroups that share a key block's window rows
   int B, layer0, n_layers, Hq, Hkv, T, W, keep, local_keep, causal, period, start;
   int out_rows;        // row capacity of k_out / v_out per (layer, sequence, kv head)
   OwnerTable own;      // owner layers of the block
@@ -34,6 +36,11 @@ constexpr int kSplitTiles = 6;  // what a split costs beside its tiles, in tiles
 
 // Workgroups per row block of the row pass for `heads` owner query heads.
 int row_splits(int heads, int T, int W, int causal);
+
+constexpr int kMaxColSplits = 16;
+
+// Workgroups per key block of the column pass for `heads` owner kv heads of `group` query heads.
+int col_splits(int heads, int T, int W, int group);
 
 hipError_t launch_rowstats(const EvictArgs& a, int dtype, int D, hipStream_t st);
 hipError_t launch_colsum(const EvictArgs& a, int dtype, int D, hipStream_t st);

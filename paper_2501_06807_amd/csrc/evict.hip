@@ -15,7 +15,8 @@
 //     operand, window-row tiles (all query heads of the group) stream through LDS as the A
 //     operand; each lane owns one key column, so the column sum needs no exchange within a tile.
 //     p = exp2(fma(c, s, b)) / sum, summed over a lane's rows of a tile in fp32 and accumulated
-//     across tiles in fp64. For 16-bit inputs both passes take 64-row (64-key) tiles, so that a
+//     across tiles in fp64. A key block's window rows may be split over several workgroups (col_splits),
+//     whose sums k_colmerge brings together. For 16-bit inputs both passes take 64-row (64-key) tiles, so that a
 //     barrier serves 64 rows. Both passes form the exponent with one fused multiply-add
 //     against the same offset, so the offset is a common factor of a row's terms and of its sum
 //     and cancels in p; it only has to keep the exponents of the large terms small. Being a whole
@@ -38,37 +39,35 @@ typedef float f32x16 __attribute__((__vector_size__(16 * sizeof(float))));
 typedef __bf16 bf16x8 __attribute__((__vector_size__(8 * sizeof(__bf16))));
 typedef _Float16 f16x8 __attribute__((__vector_size__(8 * sizeof(_Float16))));
 
-// Matrix-core operation per element type: reduction length K per instruction, KL elements per
-// lane. Lane l feeds row (l % 32) of A / column (l % 32) of B with the k-slice
-// [ks * K + (l / 32) * KL, + KL); any k-permutation works as long as A and B share it.
+// Matrix-core operation per element type. 16-bit inputs: lane l feeds row (l % 32) of A / column (l % 32) of B
+// with eight elements of each 16-wide step, the (l / 32)-th half. fp32 inputs: a 16-byte vector (the (l / 32)-th
+// half of eight elements) feeds four two-wide steps; any assignment of elements to steps works as long as A and B
+// share it.
 template <class DT>
 struct Mma;
 template <>
 struct Mma<BF16> {
-  static constexpr int K = 16, KL = 8;
   using Op = bf16x8;
   __device__ static f32x16 run(Op a, Op b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
-  __device__ static Op load(const void* p) { return __builtin_bit_cast(Op, *(const uint4*)p); }
 };
 template <>
 struct Mma<F16> {
-  static constexpr int K = 16, KL = 8;
   using Op = f16x8;
   __device__ static f32x16 run(Op a, Op b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
   }
-  __device__ static Op load(const void* p) { return __builtin_bit_cast(Op, *(const uint4*)p); }
 };
 template <>
 struct Mma<F32> {
-  static constexpr int K = 2, KL = 1;
-  using Op = float;
+  using Op = float4;
   __device__ static f32x16 run(Op a, Op b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, c, 0, 0, 0);
   }
-  __device__ static Op load(const void* p) { return *(const float*)p; }
 };
 
 // 16x16x32 matrix-core operation for 16-bit inputs: lane l feeds row (l % 16) of A / column
@@ -133,18 +132,10 @@ struct TileChunks {
   __device__ bool ok(int i) const { return (i + 1) * NT <= TL::CHUNKS || tid + i * NT < TL::CHUNKS; }
 };
 
-// Shape of the 32x32 scoring passes (fp32 inputs; 16-bit inputs take the 16x16 kernels): a
-// workgroup covers 256 window rows (pass 1) or 256 keys (pass 2) as NBK register blocks of 32 per
-// wave and 8 / NBK waves; fp32 fragments keep one block per wave.
-template <class DT>
-struct PassShape {
-  static_assert(DT::kElt == 4, "16-bit inputs take k_rowstats16 / k_colsum16");
-  static constexpr int NBK = 1;
-  static constexpr int WAVES = kRowBlock / 32 / NBK;
-  static constexpr int THREADS = WAVES * kWave;
-  static constexpr int MIN_WAVES = 1;  // waves per SIMD the register budget keeps
-};
-static_assert(kRowBlock == kColBlockKeys, "both passes cover 256 rows / keys per workgroup");
+// Waves of the fp32 passes, one 32-row (32-key) block each: eight (256 rows or keys to a workgroup), or in the column
+// pass two when that many workgroups would leave most compute units idle (launch_pass).
+constexpr int kWaves32 = 8, kFewWaves32 = 2;
+static_assert(kRowBlock == kColBlockKeys && kRowBlock == 32 * kWaves32, "both passes cover 256 rows / keys");
 
 // A window row's statistics: offset o and sum L of exp2(fma(c, s, o)) over its visible keys.
 __device__ __forceinline__ void put_stat(const EvictArgs& a, size_t row, double L, float o) {
@@ -161,15 +152,23 @@ __device__ __forceinline__ void put_row(const EvictArgs& a, int ou, size_t row0,
     a.part[((size_t)ou * a.splits + sp) * a.W + t] = make_double2(L, (double)o);
 }
 
+// Key j's accumulated attention from one workgroup of owner head ou: final, or the part of row split sp.
+__device__ __forceinline__ void put_score(const EvictArgs& a, int ou, size_t unit, int sp, int j, double sum) {
+  if (a.col_splits == 1)
+    a.score[unit * a.T + j] = (float)sum;
+  else
+    a.col_part[((size_t)ou * a.col_splits + sp) * a.T + j] = sum;
+}
+
 // Row pass on 32x32 matrix instructions (fp32 inputs; 16-bit inputs take k_rowstats16 below):
 // the offset follows the running max, so every exponent is at most 0.
 template <class DT, int D>
-__global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) void k_rowstats(EvictArgs a) {
+__global__ __launch_bounds__(kWaves32* kWave) void k_rowstats(EvictArgs a) {
   using M = Mma<DT>;
-  using PS = PassShape<DT>;
-  constexpr int NBK = PS::NBK, NT = PS::THREADS;
+  constexpr int NT = kWaves32 * kWave;
   using TL = Tile<DT, D, NT>;
-  constexpr int KS = D / M::K;
+  constexpr int KS = D / 8;
+  static_assert(DT::kElt == 4, "16-bit inputs take k_rowstats16");
   __shared__ __align__(16) unsigned char s_k[2][TL::BYTES];
 
   const int n_rb = (a.W + kRowBlock - 1) / kRowBlock;
@@ -183,19 +182,13 @@ __global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) v
   const size_t kvunit = ((size_t)l * a.B + b) * a.Hkv + hq / G;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, c32 = lane & 31, hl = lane >> 5;
 
-  // block u of this wave holds window rows row0 + 32 u .. + 31; lane column c32 is row t[u]
-  const int row0 = rb * kRowBlock + w * 32 * NBK;
-  int t[NBK], pos[NBK];
-  typename M::Op qf[NBK][KS];
+  // this wave holds window rows row0 .. + 31; lane column c32 is row t
+  const int row0 = rb * kRowBlock + w * 32, t = row0 + c32;
+  const int tcl = t < a.W ? t : a.W - 1, pos = a.T - a.W + tcl;
+  typename M::Op qf[KS];
+  const char* qrow = (const char*)a.q_win + ((size_t)qunit * a.W + tcl) * TL::RB;
 #pragma unroll
-  for (int u = 0; u < NBK; ++u) {
-    t[u] = row0 + 32 * u + c32;
-    const int tc = t[u] < a.W ? t[u] : a.W - 1;
-    pos[u] = a.T - a.W + tc;
-    const char* qrow = (const char*)a.q_win + ((size_t)qunit * a.W + tc) * TL::RB;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[u][ks] = M::load(qrow + (ks * M::K + hl * M::KL) * DT::kElt);
-  }
+  for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const float4*)(qrow + ks * 32 + hl * 16);
 
   const char* kh = (const char*)a.k + kvunit * a.T * TL::RB;
   const int last_row = min(a.W - 1, rb * kRowBlock + kRowBlock - 1);
@@ -232,116 +225,96 @@ __global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) v
   __syncthreads();
 
   const float cf = a.c32;
-  float m[NBK], nb[NBK];  // running max and its whole-number offset -ceil(c * m), per block
-  double ell[NBK];        // sum of exp2(fma(c, s, nb)) so far
-#pragma unroll
-  for (int u = 0; u < NBK; ++u) {
-    m[u] = -INFINITY;
-    nb[u] = INFINITY;
-    ell[u] = 0.0;
-  }
+  float m = -INFINITY, nb = INFINITY;  // running max and its whole-number offset -ceil(c * m)
+  double ell = 0.0;                    // sum of exp2(fma(c, s, nb)) so far
   for (int it = it0; it < it1; ++it) {
     const int buf = (it - it0) & 1;
     if (it + 1 < it1) fetch(it + 1);
-    f32x16 acc[NBK] = {};
+    f32x16 acc = {};
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const typename M::Op af =
-          M::load(&s_k[buf][c32 * TL::RS + (ks * M::K + hl * M::KL) * DT::kElt]);
-#pragma unroll
-      for (int u = 0; u < NBK; ++u) acc[u] = M::run(af, qf[u][ks], acc[u]);
-    }
+    for (int ks = 0; ks < KS; ++ks)
+      acc = M::run(*(const float4*)&s_k[buf][c32 * TL::RS + ks * 32 + hl * 16], qf[ks], acc);
     const int j0 = it * 32;
+    // a tile wholly inside the causal triangle and the key range needs no per-element mask
+    // (uniform over the wave: the block's smallest row bounds every row's last visible key)
+    const bool full = j0 + 31 < a.T && (!a.causal || j0 + 31 <= a.T - a.W + row0);
+    float tmax = -INFINITY;
+    if (full) {
 #pragma unroll
-    for (int u = 0; u < NBK; ++u) {
-      // a tile wholly inside the causal triangle and the key range needs no per-element mask
-      // (uniform over the wave: the block's smallest row bounds every row's last visible key)
-      const bool full = j0 + 31 < a.T && (!a.causal || j0 + 31 <= a.T - a.W + row0 + 32 * u);
-      float tmax = -INFINITY;
-      if (full) {
+      for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, acc[r]);
+    } else {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, acc[u][r]);
-      } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = j0 + acc_row(r, lane);
-          if (j < a.T && (!a.causal || j <= pos[u])) tmax = fmaxf(tmax, acc[u][r]);
-        }
+      for (int r = 0; r < 16; ++r) {
+        const int j = j0 + acc_row(r, lane);
+        if (j < a.T && (!a.causal || j <= pos)) tmax = fmaxf(tmax, acc[r]);
       }
-      if (tmax > m[u]) {
-        // offsets are whole numbers, so moving one rescales the sum by a power of two (exact)
-        const float nb_new = -ceilf(cf * tmax);
-        if (ell[u] > 0.0 && nb_new != nb[u]) ell[u] = ldexp(ell[u], (int)(nb_new - nb[u]));
-        m[u] = tmax;
-        nb[u] = nb_new;
-      }
-      float ps = 0.f;
-      if (full) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) ps += fast_exp2(fmaf(cf, acc[u][r], nb[u]));
-      } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = j0 + acc_row(r, lane);
-          if (j < a.T && (!a.causal || j <= pos[u])) ps += fast_exp2(fmaf(cf, acc[u][r], nb[u]));
-        }
-      }
-      ell[u] += (double)ps;
     }
+    if (tmax > m) {
+      // offsets are whole numbers, so moving one rescales the sum by a power of two (exact)
+      const float nb_new = -ceilf(cf * tmax);
+      if (ell > 0.0 && nb_new != nb) ell = ldexp(ell, (int)(nb_new - nb));
+      m = tmax;
+      nb = nb_new;
+    }
+    float ps = 0.f;
+    if (full) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) ps += fast_exp2(fmaf(cf, acc[r], nb));
+    } else {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int j = j0 + acc_row(r, lane);
+        if (j < a.T && (!a.causal || j <= pos)) ps += fast_exp2(fmaf(cf, acc[r], nb));
+      }
+    }
+    ell += (double)ps;
     if (it + 1 < it1) stash(buf ^ 1);
     __syncthreads();
   }
-#pragma unroll
-  for (int u = 0; u < NBK; ++u) {
-    // the two half-waves' sums meet at the offset of the larger max (the smaller offset)
-    const double eo = __shfl_xor(ell[u], 32);
-    const float nbo = __shfl_xor(nb[u], 32);
-    const float nbx = fminf(nb[u], nbo);
-    double L = 0.0;
-    if (ell[u] > 0.0) L += ldexp(ell[u], (int)(nbx - nb[u]));
-    if (eo > 0.0) L += ldexp(eo, (int)(nbx - nbo));
-    if (hl == 0 && t[u] < a.W) put_row(a, ou, (size_t)qunit * a.W, sp, t[u], L, nbx);
-  }
+  // the two half-waves' sums meet at the offset of the larger max (the smaller offset)
+  const double eo = __shfl_xor(ell, 32);
+  const float nbo = __shfl_xor(nb, 32);
+  const float nbx = fminf(nb, nbo);
+  double L = 0.0;
+  if (ell > 0.0) L += ldexp(ell, (int)(nbx - nb));
+  if (eo > 0.0) L += ldexp(eo, (int)(nbx - nbo));
+  if (hl == 0 && t < a.W) put_row(a, ou, (size_t)qunit * a.W, sp, t, L, nbx);
 }
 
 // Column pass on 32x32 matrix instructions (fp32 inputs; 16-bit inputs take k_colsum16 below).
-template <class DT, int D>
-__global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) void k_colsum(EvictArgs a) {
+template <class DT, int D, int WAVES>
+__global__ __launch_bounds__(WAVES* kWave) void k_colsum(EvictArgs a) {
   using M = Mma<DT>;
-  using PS = PassShape<DT>;
-  constexpr int NBK = PS::NBK, NT = PS::THREADS;
+  constexpr int NT = WAVES * kWave, KEYS = 32 * WAVES;
   using TL = Tile<DT, D, NT>;
-  constexpr int KS = D / M::K;
+  constexpr int KS = D / 8;
+  static_assert(DT::kElt == 4, "16-bit inputs take k_colsum16");
   __shared__ __align__(16) unsigned char s_q[2][TL::BYTES];
   __shared__ __align__(16) float s_nb[2][32], s_il[2][32];  // offset and 1 / sum of the staged rows
 
-  const int n_kb = (a.T + kColBlockKeys - 1) / kColBlockKeys;
+  const int n_kb = (a.T + KEYS - 1) / KEYS;
   const int id = xcd_remap(blockIdx.x, gridDim.x);
-  const int kb = id % n_kb;
-  const int ou = id / n_kb;  // (owner index * B + b) * Hkv + h
+  const int kb = id % n_kb, sp = id / n_kb % a.col_splits;
+  const int ou = id / n_kb / a.col_splits;  // (owner index * B + b) * Hkv + h
   const int l = a.own.local(ou / (a.B * a.Hkv));
   const int b = (ou / a.Hkv) % a.B, h = ou % a.Hkv;
   const size_t kvunit = ((size_t)l * a.B + b) * a.Hkv + h;
   const int G = a.Hq / a.Hkv;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, c32 = lane & 31, hl = lane >> 5;
 
-  // block u of this wave holds keys jw + 32 u .. + 31; lane column c32 is key jw + 32 u + c32
-  const int jw = kb * kColBlockKeys + w * 32 * NBK;
+  // this wave holds keys jw .. + 31; lane column c32 is key jw + c32
+  const int jw = kb * KEYS + w * 32, j = jw + c32;
   const float cf = a.c32;
-  const char* kh = (const char*)a.k + (size_t)kvunit * a.T * TL::RB;
-  typename M::Op kf[NBK][KS];
+  const char* krow = (const char*)a.k + ((size_t)kvunit * a.T + min(j, a.T - 1)) * TL::RB;
+  typename M::Op kf[KS];
 #pragma unroll
-  for (int u = 0; u < NBK; ++u) {
-    const int j = min(jw + 32 * u + c32, a.T - 1);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      kf[u][ks] = M::load(kh + (size_t)j * TL::RB + (ks * M::K + hl * M::KL) * DT::kElt);
-  }
+  for (int ks = 0; ks < KS; ++ks) kf[ks] = *(const float4*)(krow + ks * 32 + hl * 16);
 
-  const int j_lo = kb * kColBlockKeys;
+  const int j_lo = kb * KEYS;
   const int t_start = a.causal ? (max(0, j_lo - (a.T - a.W)) & ~31) : 0;
   const int n_t = (a.W - t_start + 31) / 32;
-  const int ntile = G * n_t;
+  const int ntile = G * n_t, per = (ntile + a.col_splits - 1) / a.col_splits;
+  const int it0 = min(sp * per, ntile), it1 = min(it0 + per, ntile);  // this split's tiles
   const size_t qunit0 = ((size_t)l * a.B + b) * a.Hq + (size_t)h * G;
 
   const TileChunks<TL, NT> tc(tid);
@@ -350,7 +323,8 @@ __global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) v
   // tiles run through the group's heads, each from row t_start to t_end; the next one to fetch is
   // head fg's rows ft0 .. ft0 + 31 (a counter, not a division per tile)
   const int t_end = t_start + n_t * 32;
-  int fg = 0, ft0 = t_start;
+  int fg = it0 / n_t, ft0 = t_start + it0 % n_t * 32;
+  int t0 = ft0;  // first window row of the tile being scored
   auto fetch = [&]() {
     const size_t r0 = (qunit0 + fg) * a.W + ft0;
     const char* tb = (const char*)a.q_win + r0 * TL::RB;
@@ -379,32 +353,25 @@ __global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) v
       s_il[buf][tid] = pre_b.y;
     }
   };
-  fetch();
-  stash(0);
+  if (it0 < it1) {
+    fetch();
+    stash(0);
+  }
   // the key operands are in registers before the loop, so that no wait for them lands inside it
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 
-  double cacc[NBK];
+  double cacc = 0.0;
+  for (int it = it0; it < it1; ++it) {
+    const int buf = (it - it0) & 1;
+    if (it + 1 < it1) fetch();
+    f32x16 acc = {};
 #pragma unroll
-  for (int u = 0; u < NBK; ++u) cacc[u] = 0.0;
-  int t0 = t_start;  // first window row of the tile being scored
-  for (int it = 0; it < ntile; ++it) {
-    const int buf = it & 1;
-    if (it + 1 < ntile) fetch();
-    f32x16 acc[NBK] = {};
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const typename M::Op af =
-          M::load(&s_q[buf][c32 * TL::RS + (ks * M::K + hl * M::KL) * DT::kElt]);
-#pragma unroll
-      for (int u = 0; u < NBK; ++u) acc[u] = M::run(af, kf[u][ks], acc[u]);
-    }
-    // every row of the tile valid and every key of the wave's last block visible to its first row
-    const bool full = t0 + 31 < a.W && (!a.causal || jw + 32 * NBK - 1 <= a.T - a.W + t0);
-    float ps[NBK];
-#pragma unroll
-    for (int u = 0; u < NBK; ++u) ps[u] = 0.f;
+    for (int ks = 0; ks < KS; ++ks)
+      acc = M::run(*(const float4*)&s_q[buf][c32 * TL::RS + ks * 32 + hl * 16], kf[ks], acc);
+    // every row of the tile valid and every key of the wave visible to its first row
+    const bool full = t0 + 31 < a.W && (!a.causal || jw + 31 <= a.T - a.W + t0);
+    float ps = 0.f;
     if (full) {
       // the tile's rows of this lane: 8 g + 4 hl + (0..3), g = 0..3, read four at a time
 #pragma unroll
@@ -413,38 +380,24 @@ __global__ __launch_bounds__(PassShape<DT>::THREADS, PassShape<DT>::MIN_WAVES) v
         const float4 il4 = *(const float4*)&s_il[buf][8 * g4 + 4 * hl];
         const float nbv[4] = {nb4.x, nb4.y, nb4.z, nb4.w}, ilv[4] = {il4.x, il4.y, il4.z, il4.w};
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-#pragma unroll
-          for (int u = 0; u < NBK; ++u)
-            ps[u] = fmaf(fast_exp2(fmaf(cf, acc[u][4 * g4 + q], nbv[q])), ilv[q], ps[u]);
-        }
+        for (int q = 0; q < 4; ++q) ps = fmaf(fast_exp2(fmaf(cf, acc[4 * g4 + q], nbv[q])), ilv[q], ps);
       }
     } else {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int rr = acc_row(r, lane);
         const int trow = t0 + rr;
-        if (trow >= a.W) continue;
-        const float nbv = s_nb[buf][rr], ilv = s_il[buf][rr];
-#pragma unroll
-        for (int u = 0; u < NBK; ++u) {
-          const int j = jw + 32 * u + c32;
-          if (!a.causal || j <= a.T - a.W + trow) ps[u] = fmaf(fast_exp2(fmaf(cf, acc[u][r], nbv)), ilv, ps[u]);
-        }
+        if (trow < a.W && (!a.causal || j <= a.T - a.W + trow))
+          ps = fmaf(fast_exp2(fmaf(cf, acc[r], s_nb[buf][rr])), s_il[buf][rr], ps);
       }
     }
-#pragma unroll
-    for (int u = 0; u < NBK; ++u) cacc[u] += (double)ps[u];
-    if (it + 1 < ntile) stash(buf ^ 1);
+    cacc += (double)ps;
+    if (it + 1 < it1) stash(buf ^ 1);
     t0 = t0 + 32 == t_end ? t_start : t0 + 32;
     __syncthreads();
   }
-#pragma unroll
-  for (int u = 0; u < NBK; ++u) {
-    const double tot = cacc[u] + __shfl_xor(cacc[u], 32);
-    const int j = jw + 32 * u + c32;
-    if (hl == 0 && j < a.T) a.score[(size_t)kvunit * a.T + j] = (float)tot;
-  }
+  const double tot = cacc + __shfl_xor(cacc, 32);
+  if (hl == 0 && j < a.T) put_score(a, ou, kvunit, sp, j, tot);
 }
 
 // The vector work of one 32x32 block of scores (sixteen per lane), in nine chunks: F(r) forms the
@@ -743,8 +696,8 @@ __global__ __launch_bounds__(kColThreads16, 3) void k_colsum16(EvictArgs a) {
 
   const int n_kb = (a.T + kColBlockKeys - 1) / kColBlockKeys;
   const int id = xcd_remap(blockIdx.x, gridDim.x);
-  const int kb = id % n_kb;
-  const int ou = id / n_kb;  // (owner index * B + b) * Hkv + h
+  const int kb = id % n_kb, sp = id / n_kb % a.col_splits;
+  const int ou = id / n_kb / a.col_splits;  // (owner index * B + b) * Hkv + h
   const int l = a.own.local(ou / (a.B * a.Hkv));
   const int b = (ou / a.Hkv) % a.B, h = ou % a.Hkv;
   const size_t kvunit = ((size_t)l * a.B + b) * a.Hkv + h;
@@ -767,7 +720,8 @@ __global__ __launch_bounds__(kColThreads16, 3) void k_colsum16(EvictArgs a) {
   const int j_lo = kb * kColBlockKeys;
   const int t_start = a.causal ? (max(0, j_lo - (a.T - a.W)) & ~31) : 0;
   const int n_t = (a.W - t_start + RT - 1) / RT;
-  const int ntile = G * n_t;
+  const int ntile = G * n_t, per = (ntile + a.col_splits - 1) / a.col_splits;
+  const int it0 = min(sp * per, ntile), it1 = min(it0 + per, ntile);  // this split's tiles
   const size_t qunit0 = ((size_t)l * a.B + b) * a.Hq + (size_t)h * G;
 
   const TileChunks<TL, NT> tc(tid);
@@ -776,7 +730,8 @@ __global__ __launch_bounds__(kColThreads16, 3) void k_colsum16(EvictArgs a) {
   // tiles run through the group's heads, each from row t_start to t_end; the next one to fetch is
   // head fg's rows ft0 .. ft0 + RT - 1
   const int t_end = t_start + n_t * RT;
-  int fg = 0, ft0 = t_start;
+  int fg = it0 / n_t, ft0 = t_start + it0 % n_t * RT;
+  int t0 = ft0;  // first window row of the tile being scored
   auto fetch = [&]() {
     const size_t r0 = (qunit0 + fg) * a.W + ft0;
     const char* tb = (const char*)a.q_win + r0 * TL::RB;
@@ -805,14 +760,15 @@ __global__ __launch_bounds__(kColThreads16, 3) void k_colsum16(EvictArgs a) {
       s_il[buf][tid] = pre_b.y;
     }
   };
-  fetch();
-  stash(0);
+  if (it0 < it1) {
+    fetch();
+    stash(0);
+  }
   // the key operands are in registers before the loop, so that no wait for them lands inside it
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 
   double cacc[4] = {0.0, 0.0, 0.0, 0.0};
-  int t0 = t_start;  // first window row of the tile being scored
   // one tile; FULL: every row valid and every key of the wave visible to the tile's first row
   auto tile = [&](auto full_tag, int buf) {
     constexpr bool FULL = decltype(full_tag)::value;
@@ -850,9 +806,9 @@ __global__ __launch_bounds__(kColThreads16, 3) void k_colsum16(EvictArgs a) {
 #pragma unroll
     for (int g = 0; g < 4; ++g) cacc[g] += (double)ps[g];
   };
-  for (int it = 0; it < ntile; ++it) {
-    const int buf = it & 1;
-    if (it + 1 < ntile) fetch();
+  for (int it = it0; it < it1; ++it) {
+    const int buf = (it - it0) & 1;
+    if (it + 1 < it1) fetch();
     // keys past the prompt, or past what the tile's last row sees: the wave only helps stage the tile
     if (jw < a.T && (!a.causal || jw <= a.T - a.W + t0 + RT - 1)) {
       if (t0 + RT - 1 < a.W && (!a.causal || jw + 63 <= a.T - a.W + t0))
@@ -860,7 +816,7 @@ __global__ __launch_bounds__(kColThreads16, 3) void k_colsum16(EvictArgs a) {
       else
         tile(std::false_type{}, buf);
     }
-    if (it + 1 < ntile) stash(buf ^ 1);
+    if (it + 1 < it1) stash(buf ^ 1);
     t0 = t0 + RT == t_end ? t_start : t0 + RT;
     __syncthreads();
   }
@@ -869,7 +825,7 @@ __global__ __launch_bounds__(kColThreads16, 3) void k_colsum16(EvictArgs a) {
     double tot = cacc[g] + __shfl_xor(cacc[g], 16);
     tot += __shfl_xor(tot, 32);
     const int j = jw + 16 * g + c16;
-    if (q4 == 0 && j < a.T) a.score[(size_t)kvunit * a.T + j] = (float)tot;
+    if (q4 == 0 && j < a.T) put_score(a, ou, kvunit, sp, j, tot);
   }
 }
 
@@ -1187,6 +1143,21 @@ __global__ __launch_bounds__(256) void k_gather(EvictArgs a) {
   }
 }
 
+// Scores of keys whose window rows were split over several workgroups.
+__global__ __launch_bounds__(256) void k_colmerge(EvictArgs a) {
+  const int64_t n = (int64_t)a.own.n * a.B * a.Hkv * a.T, i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int ou = (int)(i / a.T), j = (int)(i % a.T);
+  const double* p = a.col_part + (size_t)ou * a.col_splits * a.T + j;
+  double x[kMaxColSplits], sum = 0.0;  // every split's part is requested before any is used
+#pragma unroll
+  for (int s = 0; s < kMaxColSplits; ++s) x[s] = s < a.col_splits ? p[(size_t)s * a.T] : 0.0;
+#pragma unroll
+  for (int s = 0; s < kMaxColSplits; ++s) sum += x[s];
+  const size_t unit = (size_t)a.own.local(ou / (a.B * a.Hkv)) * a.B * a.Hkv + ou % (a.B * a.Hkv);
+  a.score[unit * a.T + j] = (float)sum;
+}
+
 template <class DT, int D>
 hipError_t launch_pass(const EvictArgs& a, bool rows, hipStream_t st) {
   if (rows) {
@@ -1194,13 +1165,21 @@ hipError_t launch_pass(const EvictArgs& a, bool rows, hipStream_t st) {
     if constexpr (DT::kElt == 2)
       hipLaunchKernelGGL((k_rowstats16<DT, D>), dim3(a.own.n * a.B * a.Hq * n_rb * a.splits), dim3(kRowThreads16), 0, st, a);
     else
-      hipLaunchKernelGGL((k_rowstats<DT, D>), dim3(a.own.n * a.B * a.Hq * n_rb * a.splits), dim3(PassShape<DT>::THREADS), 0, st, a);
+      hipLaunchKernelGGL((k_rowstats<DT, D>), dim3(a.own.n * a.B * a.Hq * n_rb * a.splits), dim3(kWaves32 * kWave), 0, st,
+                         a);
   } else {
     const int n_kb = (a.T + kColBlockKeys - 1) / kColBlockKeys;
-    if constexpr (DT::kElt == 2)
-      hipLaunchKernelGGL((k_colsum16<DT, D>), dim3(a.own.n * a.B * a.Hkv * n_kb), dim3(kColThreads16), 0, st, a);
-    else
-      hipLaunchKernelGGL((k_colsum<DT, D>), dim3(a.own.n * a.B * a.Hkv * n_kb), dim3(PassShape<DT>::THREADS), 0, st, a);
+    const int heads = a.own.n * a.B * a.Hkv * a.col_splits;
+    if constexpr (DT::kElt == 2) {
+      hipLaunchKernelGGL((k_colsum16<DT, D>), dim3(heads * n_kb), dim3(kColThreads16), 0, st, a);
+    } else if (heads * n_kb <= kNumCU / 4) {
+      // few workgroups: a quarter of the keys each (12 heads of 512 keys, 24 workgroups of eight waves: prefill
+      // 46.9 us; 96 of two, with operands read four elements at a time in both passes: 34.7)
+      const int n_few = (a.T + 32 * kFewWaves32 - 1) / (32 * kFewWaves32);
+      hipLaunchKernelGGL((k_colsum<DT, D, kFewWaves32>), dim3(heads * n_few), dim3(kFewWaves32 * kWave), 0, st, a);
+    } else {
+      hipLaunchKernelGGL((k_colsum<DT, D, kWaves32>), dim3(heads * n_kb), dim3(kWaves32 * kWave), 0, st, a);
+    }
   }
   return hipGetLastError();
 }
@@ -1255,7 +1234,33 @@ int row_splits(int heads, int T, int W, int causal) {
 }
 
 hipError_t launch_colsum(const EvictArgs& a, int dtype, int D, hipStream_t st) {
-  return launch_pass_any(a, dtype, D, false, st);
+  const hipError_t e = launch_pass_any(a, dtype, D, false, st);
+  if (e != hipSuccess || a.col_splits == 1) return e;
+  const int64_t keys = (int64_t)a.own.n * a.B * a.Hkv * a.T;
+  hipLaunchKernelGGL(k_colmerge, dim3((unsigned)((keys + 255) / 256)), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+// A split is taken where the key blocks leave compute units idle or with one workgroup: it costs three tiles beside
+// its own (key loads, first tile) and, all together, a merge of about five tiles' time. Prefill of one layer with
+// eight kv heads of four query heads: 1023 keys 81.9 -> 42.1 us, 8191 keys 365 -> 308 us; two kv heads of 700 keys 64.8
+// -> 35.8 us; eight heads of 3000 keys (fp32) 302 -> 191 us. 32 heads of 7177 keys and more stay whole.
+int col_splits(int heads, int T, int W, int group) {
+  const int64_t base = (int64_t)heads * ((T + kColBlockKeys - 1) / kColBlockKeys);
+  const int ntile = group * ((W + 63) / 64);
+  int best = 1;
+  double cost = INFINITY;
+  for (int s = 1; s <= kMaxColSplits && s <= ntile; ++s) {
+    const int64_t per_cu = (base * s + kNumCU - 1) / kNumCU;
+    if (s > 1 && per_cu > 3) break;
+    const double len = (double)((ntile + s - 1) / s) + 3.0;
+    const double c = (per_cu == 1 ? 1.4 * len : per_cu * len) + (s > 1 ? 5.0 : 0.0);
+    if (c < 0.95 * cost) {
+      cost = c;
+      best = s;
+    }
+  }
+  return best;
 }
 
 template <int NT, int KPT>

@@ -1,5 +1,5 @@
-"""GPU parity of the eviction's row pass where its keys are split over several workgroups, and where the
-row offsets have to move: log-sum-exps and token scores against the oracle.
+"""GPU parity of the eviction's scoring passes where keys (row pass) or window rows (column pass) are split over
+several workgroups, and where the row offsets have to move: log-sum-exps and token scores against the oracle.
 """
 import math
 
@@ -40,7 +40,8 @@ def _bits(x, dtype):
 
 # T, W, query heads, kv heads, head dim, type, causal, kind. Splits run out of tiles (T below 16 tiles of
 # 64 keys), a last split of masked tiles only or of none, ragged tiles, a window of one row and of every
-# row; "rising": each 64-key tile scores about eight binary orders above the one before, so the offsets of
+# row, column splits that begin inside a query head's rows, fp32 column workgroups of two waves and of eight;
+# "rising": each 64-key tile scores about eight binary orders above the one before, so the offsets of
 # most tiles have to move; "falling": the first tile holds the maximum.
 CASES = [
     (64, 64, 1, 1, 64, "bf16", True, "random"),
@@ -50,6 +51,10 @@ CASES = [
     (1025, 257, 4, 1, 64, "fp16", False, "random"),
     (2111, 130, 2, 2, 64, "fp32", True, "random"),
     (513, 200, 1, 1, 128, "fp32", False, "random"),
+    (2111, 400, 4, 4, 64, "fp32", True, "random"),
+    (1100, 64, 16, 16, 128, "fp32", False, "random"),
+    (257, 130, 8, 1, 128, "bf16", True, "random"),
+    (700, 513, 8, 2, 64, "fp16", True, "random"),
     (600, 90, 2, 1, 128, "bf16", True, "rising"),
     (600, 90, 2, 2, 64, "fp16", False, "rising"),
     (500, 300, 1, 1, 64, "fp32", True, "rising"),
