@@ -113,7 +113,8 @@ enum { MPC_OP_STATIC_EVICT = 0, MPC_OP_SELECT = 1, MPC_OP_DECODE_ATTN = 2, MPC_O
 /* Workspace bytes needed by `op` (MPC_OP_*) for these dims. `T_or_Ts` is T for static eviction
  * and Ts otherwise; `cfg` points to the op's config struct (mpc_evict_cfg for static eviction,
  * mpc_select_cfg for selection and the decode step) or is NULL for MPC_OP_DECODE_ATTN. Returns 0
- * when the op needs no workspace or the arguments are invalid. */
+ * when the op needs no workspace or the arguments are invalid. The size for static eviction never falls
+ * with a dimension, T or the window, so one made for the longest prompt serves the shorter ones. */
 size_t mpc_workspace_bytes(int32_t op, const mpc_dims* dims, int32_t T_or_Ts, const void* cfg);
 
 /* Look-once static eviction (Sec. 3.2; Alg. 3 step 1; window rule of App. F).

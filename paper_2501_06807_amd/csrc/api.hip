@@ -80,8 +80,13 @@ constexpr size_t kScratchBytes = (size_t)32 << 20;  // static array of mpc_stati
 
 // Static eviction workspace: the (exponent offset, 1 / sum) pair of every window row, then fp32
 // token scores, then the column pass's partials. The row pass's partials take the place of both before (they are
-// merged by the time the column pass starts). Splits are taken only as far as a block that fits the static array
-// without them stays inside it: no block is refused for its splits, and both entry points split alike.
+// merged by the time the column pass starts). The size is that of rows and scores, which grows with every dimension,
+// and a fixed room for partials, not what the splits of these sizes take: fewer keys may take more splits, and a
+// workspace made for the longest prompt has to serve the shorter ones. A block whose rows and scores fit the static
+// array of mpc_static_evict_noalloc stays inside it, so that no block is refused for its splits and both entry
+// points split alike. 16 MiB hold the splits of every block up to about 4000 row blocks of 256 rows.
+constexpr size_t kSplitRoom = (size_t)16 << 20;
+
 struct EvictWs {
   size_t rowstat, score, col_part, total;
   int splits, col_splits;
@@ -92,20 +97,14 @@ EvictWs evict_ws(const mpc_dims* d, int T, const mpc_evict_cfg* cfg) {
   w.rowstat = 0;
   w.score = align256((size_t)d->n_layers * d->batch * d->n_q_heads * W * sizeof(double));
   w.col_part = w.score + align256((size_t)d->n_layers * d->batch * d->n_kv_heads * T * sizeof(float));
+  w.total = w.col_part + kSplitRoom;
+  if (w.col_part <= kScratchBytes) w.total = std::min(w.total, kScratchBytes);
   const mpc::OwnerTable own = mpc::owner_table(d->layer0, d->n_layers, cfg->share_period, cfg->share_start);
   const size_t heads = (size_t)own.n * d->batch * d->n_q_heads, kv_heads = (size_t)own.n * d->batch * d->n_kv_heads;
   w.splits = own.n > 0 ? mpc::row_splits((int)heads, T, W, cfg->causal) : 1;
   w.col_splits = own.n > 0 ? mpc::col_splits((int)kv_heads, T, W, d->n_q_heads / d->n_kv_heads) : 1;
-  auto total = [&]() {
-    const size_t rows = w.splits > 1 ? w.score + align256(heads * w.splits * W * sizeof(double2)) : 0;
-    const size_t cols = w.col_splits > 1 ? w.col_part + align256(kv_heads * w.col_splits * T * sizeof(double)) : 0;
-    return std::max(w.col_part, std::max(rows, cols));
-  };
-  if (w.col_part <= kScratchBytes) {
-    while (w.col_splits > 1 && total() > kScratchBytes) --w.col_splits;
-    while (w.splits > 1 && total() > kScratchBytes) --w.splits;
-  }
-  w.total = total();
+  while (w.splits > 1 && w.score + heads * w.splits * W * sizeof(double2) > w.total) --w.splits;
+  while (w.col_splits > 1 && w.col_part + kv_heads * w.col_splits * T * sizeof(double) > w.total) --w.col_splits;
   return w;
 }
 
@@ -746,7 +745,7 @@ mpc_status mpc_static_evict_noalloc(const mpc_dims* dims, int32_t T, const mpc_e
   mpc_status s = prepare_evict(dims, T, cfg, q_win, k, v, kept_idx, k_out, v_out, token_score, row_lse, nullptr, 0,
                                &unused);
   if (s != MPC_EWORKSPACE) return s;
-  const size_t need = evict_ws(dims, T, cfg).total;
+  const size_t need = evict_ws(dims, T, cfg).col_part;  // rows and scores: splits take what is left
   if (need > kScratchBytes)
     return fail(MPC_EWORKSPACE, "static eviction of this block needs %zu scratch bytes, the static array holds %zu "
                 "(call it on fewer layers or sequences)", need, kScratchBytes);

@@ -188,6 +188,29 @@ def test_static_evict_validation_and_workspace():
     assert s == L.MPC_EINVAL
 
 
+def test_evict_workspace_of_the_longest_prompt_serves_the_shorter_ones():
+    """The workspace of a block covers every block of no more tokens, window rows, layers, sequences or heads
+    (a program makes it once, for its longest prompt), and a block whose rows and scores fit the static scratch
+    array stays inside it."""
+    def need(n_layers, batch, n_q_heads, n_kv_heads, T, W):
+        d = _dims(n_layers=n_layers, batch=batch, n_q_heads=n_q_heads, n_kv_heads=n_kv_heads)
+        cfg = L.MpcEvictCfg(window=W, keep=32, local_keep=32, sm_scale=0.088, causal=1, share_period=1, share_start=2)
+        base = n_layers * batch * (n_q_heads * W * 8 + n_kv_heads * T * 4)
+        got = L.workspace_bytes(L.MPC_OP_STATIC_EVICT, d, T, cfg)
+        assert got >= base and (got <= 32 << 20 or base > (32 << 20) - 512), (n_layers, batch, T, W, got)
+        return got
+
+    for n_layers, batch, hq, hkv in ((1, 1, 2, 2), (1, 1, 32, 32), (1, 1, 32, 8), (4, 1, 32, 8), (12, 1, 12, 12), (4, 4, 32, 32)):
+        for share in (5, 10):
+            lengths = [64, 300, 512, 700, 1023, 2048, 3000, 4111, 7177, 8192, 16000, 32768, 40000, 131072]
+            sizes = [need(n_layers, batch, hq, hkv, T, max(1, T // share)) for T in lengths]
+            assert sizes == sorted(sizes), (n_layers, batch, hq, hkv, share, sizes)
+    for T in (512, 7177, 32768):
+        for grow in ([need(n, 1, 32, 32, T, T // 5) for n in (1, 2, 3, 4, 8)], [need(1, n, 32, 32, T, T // 5) for n in (1, 2, 3, 4, 8)],
+                     [need(1, 1, h, h, T, T // 5) for h in (1, 2, 8, 12, 32, 64)], [need(1, 1, 32, 32, T, W) for W in (1, 9, 100, 512)]):
+            assert grow == sorted(grow), (T, grow)
+
+
 def test_prefill_validation():
     d = _dims(n_layers=4, batch=1, n_q_heads=8, n_kv_heads=2)
     ecfg = L.MpcEvictCfg(window=100, keep=200, local_keep=32, sm_scale=0.088, causal=1, share_period=2,
