@@ -245,6 +245,8 @@ mpc_status prepare_evict(const mpc_dims* dims, int32_t T, const mpc_evict_cfg* c
   a.start = cfg->share_start;
   a.own = mpc::owner_table(dims->layer0, dims->n_layers, cfg->share_period, cfg->share_start);
   a.c32 = (float)((double)cfg->sm_scale * 1.4426950408889634);
+  a.col_group = mpc::col_group(a.own.n * a.B * a.Hkv * a.col_splits, T, (int64_t)(a.Hq / a.Hkv) * a.W * dims->head_dim *
+                                   elt_size(dims->dtype) / a.col_splits + 1);
   *out = a;
   return MPC_OK;
 }

@@ -24,6 +24,7 @@ struct EvictArgs {
   int splits;          // workgroups that share a row block's keys
   double* col_part;    // column pass partials [owner heads][col_splits][T]; unused with one split
   int col_splits;      // workgroups that share a key block's window rows
+  int col_group;       // 16-bit column-pass units whose key blocks are dealt together (col_group below)
   int B, layer0, n_layers, Hq, Hkv, T, W, keep, local_keep, causal, period, start;
   int out_rows;        // row capacity of k_out / v_out per (layer, sequence, kv head)
   OwnerTable own;      // owner layers of the block
@@ -41,6 +42,9 @@ constexpr int kMaxColSplits = 16;
 
 // Workgroups per key block of the column pass for `heads` owner kv heads of `group` query heads.
 int col_splits(int heads, int T, int W, int group);
+
+// Units (owner kv heads times row splits) of the 16-bit column pass to a group; unit_bytes: window rows a unit reads.
+int col_group(int units, int T, int64_t unit_bytes);
 
 hipError_t launch_rowstats(const EvictArgs& a, int dtype, int D, hipStream_t st);
 hipError_t launch_colsum(const EvictArgs& a, int dtype, int D, hipStream_t st);

@@ -40,7 +40,8 @@ def _bits(x, dtype):
 
 # T, W, query heads, kv heads, head dim, type, causal, kind. Splits run out of tiles (T below 16 tiles of
 # 64 keys), a last split of masked tiles only or of none, ragged tiles, a window of one row and of every
-# row, column splits that begin inside a query head's rows, fp32 column workgroups of two waves and of eight;
+# row, column splits that begin inside a query head's rows, fp32 column workgroups of two waves and of eight, groups of
+# several column units with a last one of fewer;
 # "rising": each 64-key tile scores about eight binary orders above the one before, so the offsets of
 # most tiles have to move; "falling": the first tile holds the maximum.
 CASES = [
@@ -55,6 +56,9 @@ CASES = [
     (1100, 64, 16, 16, 128, "fp32", False, "random"),
     (257, 130, 8, 1, 128, "bf16", True, "random"),
     (700, 513, 8, 2, 64, "fp16", True, "random"),
+    (2000, 20, 100, 100, 64, "bf16", True, "random"),
+    (900, 700, 203, 203, 64, "fp16", True, "random"),
+    (1025, 1025, 160, 160, 64, "bf16", True, "random"),
     (600, 90, 2, 1, 128, "bf16", True, "rising"),
     (600, 90, 2, 2, 64, "fp16", False, "rising"),
     (500, 300, 1, 1, 64, "fp32", True, "rising"),
