@@ -18,7 +18,7 @@ struct EvictArgs {
   void* k_out;         // [L][B][Hkv][out_rows][d], rows [0, keep) written
   void* v_out;
   float* score;        // [L][B][Hkv][T] accumulated attention (token_score or workspace)
-  float2* rowstat;     // [L][B][Hq][W]: (whole-number offset b, every fma(c, score, b) <= 5; 1 / sum of exp2(fma(c, score, b)))
+  float2* rowstat;     // [L][B][Hq][W]: (whole-number offset b, every fma(c, score, b) <= 1; 1 / sum of exp2(fma(c, score, b)))
   float* row_lse;      // [L][B][Hq][W] natural log-sum-exp, optional
   double2* part;       // row pass partials [owner heads][splits][W]: (sum, offset); unused with one split
   int splits;          // workgroups that share a row block's keys
@@ -33,7 +33,7 @@ struct EvictArgs {
 };
 
 constexpr int kMaxRowSplits = 16;
-constexpr int kSplitTiles = 6;  // what a split costs beside its tiles, in tiles
+constexpr int kSplitTiles = 2;  // what a split costs beside its tiles, in tiles
 
 // Workgroups per row block of the row pass for `heads` owner query heads.
 int row_splits(int heads, int T, int W, int causal);

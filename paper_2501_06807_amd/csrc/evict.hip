@@ -3,12 +3,11 @@
 // The accumulated attention of key j is A[j] = sum over the group's window rows t of
 // softmax_j(sm_scale * q_t . k_j). It needs every row's normaliser before any column can be
 // summed, so it takes two passes over the scores, both on the matrix cores (16-bit inputs:
-// v_mfma_f32_32x32x16_{bf16,f16} in the row pass, 16x16x32 in the column pass; fp32 inputs:
-// v_mfma_f32_32x32x2f32):
-//   pass 1 (k_rowstats16, k_rowstats for fp32): window rows stay in registers as the B operand,
-//     key tiles stream through LDS as the A operand; each lane owns one query column of its
+// v_mfma_f32_16x16x32_{bf16,f16}; fp32 inputs: v_mfma_f32_32x32x2f32):
+//   pass 1 (k_rowstats16 for 16-bit inputs, k_rowstats for fp32): window rows stay in registers as the
+//     B operand, key tiles stream through LDS as the A operand; each lane owns one query column of its
 //     blocks, so a row's sum needs no exchange until the end. Output per row: a whole-number
-//     offset b with every exponent fma(c, s, b) at most 5 (b = -ceil(fp32(c * m)) for fp32 inputs, m the
+//     offset b with every exponent fma(c, s, b) at most 1 (b = -ceil(fp32(c * m)) for fp32 inputs, m the
 //     row max), and 1 / sum of exp2(fma(c, s, b)), c = fp32(sm_scale * log2(e)). A row block's keys
 //     may be split over several workgroups (row_splits), whose sums k_rowmerge brings together.
 //   pass 2 (k_colsum16 for 16-bit inputs, k_colsum for fp32): keys stay in registers as the B
@@ -21,9 +20,8 @@
 //     against the same offset, so the offset is a common factor of a row's terms and of its sum
 //     and cancels in p; it only has to keep the exponents of the large terms small. Being a whole
 //     number, a move of the offset rescales pass 1's sums by an exact power of two (ldexp). The
-//     exponents of the terms near the max lie in (-2, 5] (16-bit inputs; nearly always below 4), so
-//     their rounding, and that of c (proportional to |c * (s - m)|), stay smallest on the terms that
-//     carry the sums.
+//     exponents of the terms near the max lie in (-1, 1], so their rounding, and that of c
+//     (proportional to |c * (s - m)|), stay smallest on the terms that carry the sums.
 // The top-k is an 8-bit LDS radix select on the fp32 score bits followed by an ordered block
 // compaction, each thread's run of scores held in registers up to 32K older tokens; the
 // gather copies kept rows with 16-byte lanes (all layers, or those whose representatives are not
@@ -40,36 +38,15 @@ typedef float f32x16 __attribute__((__vector_size__(16 * sizeof(float))));
 typedef __bf16 bf16x8 __attribute__((__vector_size__(8 * sizeof(__bf16))));
 typedef _Float16 f16x8 __attribute__((__vector_size__(8 * sizeof(_Float16))));
 
-// Matrix-core operation per element type. 16-bit inputs: lane l feeds row (l % 32) of A / column (l % 32) of B
-// with eight elements of each 16-wide step, the (l / 32)-th half. fp32 inputs: a 16-byte vector (the (l / 32)-th
-// half of eight elements) feeds four two-wide steps; any assignment of elements to steps works as long as A and B
-// share it.
-template <class DT>
-struct Mma;
-template <>
-struct Mma<BF16> {
-  using Op = bf16x8;
-  __device__ static f32x16 run(Op a, Op b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  }
-};
-template <>
-struct Mma<F16> {
-  using Op = f16x8;
-  __device__ static f32x16 run(Op a, Op b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
-  }
-};
-template <>
-struct Mma<F32> {
-  using Op = float4;
-  __device__ static f32x16 run(Op a, Op b, f32x16 c) {
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, c, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, c, 0, 0, 0);
-  }
-};
+// 32x32x2 matrix-core operations of fp32 inputs on a 16-byte vector per lane: lane l feeds row (l % 32) of A /
+// column (l % 32) of B with the (l / 32)-th half of eight elements, four two-wide steps; any assignment of
+// elements to steps works as long as A and B share it.
+__device__ __forceinline__ f32x16 mma32(float4 a, float4 b, f32x16 c) {
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, c, 0, 0, 0);
+}
 
 // 16x16x32 matrix-core operation for 16-bit inputs: lane l feeds row (l % 16) of A / column
 // (l % 16) of B with the k-slice [(l / 16) * 8, + 8) of each 32-wide step, and receives the output
@@ -185,7 +162,6 @@ __device__ __forceinline__ void put_score(const EvictArgs& a, int ou, size_t uni
 // the offset follows the running max, so every exponent is at most 0.
 template <class DT, int D>
 __global__ __launch_bounds__(kWaves32* kWave) void k_rowstats(EvictArgs a) {
-  using M = Mma<DT>;
   constexpr int NT = kWaves32 * kWave;
   using TL = Tile<DT, D, NT>;
   constexpr int KS = D / 8;
@@ -206,7 +182,7 @@ __global__ __launch_bounds__(kWaves32* kWave) void k_rowstats(EvictArgs a) {
   // this wave holds window rows row0 .. + 31; lane column c32 is row t
   const int row0 = rb * kRowBlock + w * 32, t = row0 + c32;
   const int tcl = t < a.W ? t : a.W - 1, pos = a.T - a.W + tcl;
-  typename M::Op qf[KS];
+  float4 qf[KS];
   const char* qrow = (const char*)a.q_win + ((size_t)qunit * a.W + tcl) * TL::RB;
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const float4*)(qrow + ks * 32 + hl * 16);
@@ -254,7 +230,7 @@ __global__ __launch_bounds__(kWaves32* kWave) void k_rowstats(EvictArgs a) {
     f32x16 acc = {};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      acc = M::run(*(const float4*)&s_k[buf][c32 * TL::RS + ks * 32 + hl * 16], qf[ks], acc);
+      acc = mma32(*(const float4*)&s_k[buf][c32 * TL::RS + ks * 32 + hl * 16], qf[ks], acc);
     const int j0 = it * 32;
     // a tile wholly inside the causal triangle and the key range needs no per-element mask
     // (uniform over the wave: the block's smallest row bounds every row's last visible key)
@@ -305,7 +281,6 @@ __global__ __launch_bounds__(kWaves32* kWave) void k_rowstats(EvictArgs a) {
 // Column pass on 32x32 matrix instructions (fp32 inputs; 16-bit inputs take k_colsum16 below).
 template <class DT, int D, int WAVES>
 __global__ __launch_bounds__(WAVES* kWave) void k_colsum(EvictArgs a) {
-  using M = Mma<DT>;
   constexpr int NT = WAVES * kWave, KEYS = 32 * WAVES;
   using TL = Tile<DT, D, NT>;
   constexpr int KS = D / 8;
@@ -327,7 +302,7 @@ __global__ __launch_bounds__(WAVES* kWave) void k_colsum(EvictArgs a) {
   const int jw = kb * KEYS + w * 32, j = jw + c32;
   const float cf = a.c32;
   const char* krow = (const char*)a.k + ((size_t)kvunit * a.T + min(j, a.T - 1)) * TL::RB;
-  typename M::Op kf[KS];
+  float4 kf[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) kf[ks] = *(const float4*)(krow + ks * 32 + hl * 16);
 
@@ -389,7 +364,7 @@ __global__ __launch_bounds__(WAVES* kWave) void k_colsum(EvictArgs a) {
     f32x16 acc = {};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      acc = M::run(*(const float4*)&s_q[buf][c32 * TL::RS + ks * 32 + hl * 16], kf[ks], acc);
+      acc = mma32(*(const float4*)&s_q[buf][c32 * TL::RS + ks * 32 + hl * 16], kf[ks], acc);
     // every row of the tile valid and every key of the wave visible to its first row
     const bool full = t0 + 31 < a.W && (!a.causal || jw + 31 <= a.T - a.W + t0);
     float ps = 0.f;
@@ -421,60 +396,26 @@ __global__ __launch_bounds__(WAVES* kWave) void k_colsum(EvictArgs a) {
   if (hl == 0 && j < a.T) put_score(a, ou, kvunit, sp, j, tot);
 }
 
-// The vector work of one 32x32 block of scores (sixteen per lane), in nine chunks: F(r) forms the
-// exponent of score r, E(r) takes its exp2, A(r) adds it up. Chunk 0 opens the block (three
-// operations), chunks 1..7 carry two scores each (six operations, the exp2s apart from one another and
-// from their uses), chunk 8 closes it. Every chunk ends with a scheduling barrier, so the chunks stay
-// where the caller writes them between another block's matrix instructions.
-template <int CHUNK, class F, class E, class A>
-__device__ __forceinline__ void block_chunk(F f, E e, A add) {
-  if constexpr (CHUNK == 0) {
-    f(0);
-    f(1);
-    e(0);
-  } else if constexpr (CHUNK < 8) {
-    e(2 * CHUNK - 1);
-    f(2 * CHUNK);
-    f(2 * CHUNK + 1);
-    e(2 * CHUNK);
-    add(2 * CHUNK - 2);
-    add(2 * CHUNK - 1);
-  } else {
-    e(15);
-    add(14);
-    add(15);
-  }
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// Keeps a value computed here from being moved to its use.
-__device__ __forceinline__ void pin(float& x) { asm volatile("" : "+v"(x)); }
-
-// Row pass for 16-bit inputs, on 32x32x16 matrix instructions. A wave holds 64 window rows in
-// registers as two 32-row B operands and takes each 64-key tile from LDS as two 32-key A operands: four
-// 32x32 blocks, whose vector work (fma, exp2, add for each of a lane's sixteen scores of one row) runs
-// between the matrix instructions of the block after it, in the order written out below. Left to the
-// compiler, a block's chain and its exponentials follow one another with idle cycles between, and the
-// 16x16x32 instruction costs twice the issue time for the same work: in a register-only loop with three
-// waves per SIMD, 64 scores take 8.9 ns this way, 10.7 ns with 16x16x32 instructions.
+// Row pass for 16-bit inputs on 16x16x32 matrix instructions. A wave holds 64 window rows in
+// registers as four 16-row B operands (query groups) and takes each 64-key tile from LDS as four
+// 16-key A operands, so a tile is sixteen 16x16 blocks; a lane holds keys 4 (lane / 16) + r of one
+// row per block. Each block's exponentials are taken against the row's current offset, with no
+// running max, beside the next block's matrix chain (one basic block, so the two interleave). A
+// block whose four terms sum to at most 2 has every exponent at most 1, as accurate as an offset
+// at the max; a larger sum takes the slow path: the offset moves to the block's max if that is
+// higher (the running sums rescaled by an exact power of two) and the block is summed again. The
+// four lanes of a row meet once at the end at the smallest offset, so no exponent of pass 2 exceeds 1.
 //
-// The exponents are taken against an offset set from the wave's first tile, one below that tile's row
-// max, and kept while the largest terms of a tile stay within 2^5: a tile in which a lane's 32 terms of a
-// row sum to more than 32 is done again after its maxima have moved the offset (its scores still in LDS;
-// about one tile in a hundred on random prompts of 32K keys). So no per-block test splits the loop.
-//
-// What bounds it: the chip's power. At 4 x 32768 keys and 32 heads the matrix cores are busy 64% of the
-// cycles, at 1.8 GHz (52% at 2.0 GHz with 16x16x32 blocks and a test per block): 3.90 -> 3.50 ms, and
-// 3.25 ms with the keys split in two, 1.03 PFLOP/s beside a bf16 matrix product's 1.32 on this card.
-// Short of work for every compute unit (row_splits), the splits count for more: 32 heads of 7177 keys
-// 220 -> 148 us, 100 us split in four.
+// 32x32x16 blocks in a written-out order, with their offsets checked once per tile of 64 keys, were 2 to 8% faster
+// (a prefill of 32 x 8192 keys) only while exponents up to 5 were let through, which doubled the largest
+// error of a score on peaked rows. Held to exponents of at most 1 they were no faster (eviction of eight layers of 8192
+// keys and 32 heads: 1880 us here, 1898 us so; with scores of three times the spread 1944 and 2104 us).
 template <class DT, int D>
 __global__ __launch_bounds__(kRowThreads16, 3) void k_rowstats16(EvictArgs a) {
-  using M = Mma<DT>;
   constexpr int NT = kRowThreads16;
   constexpr int KT = 64;  // keys per staged tile
   using TL = Tile<DT, D, NT, KT>;
-  constexpr int KS = D / 16;
+  constexpr int KS = D / 32;
   static_assert(DT::kElt == 2, "16-bit inputs");
   static_assert(NT / kWave * 64 == kRowBlock, "four waves of 64 rows");
   __shared__ __align__(16) unsigned char s_k[2][TL::BYTES];
@@ -488,21 +429,20 @@ __global__ __launch_bounds__(kRowThreads16, 3) void k_rowstats16(EvictArgs a) {
   const size_t qunit = ((size_t)l * a.B + b) * a.Hq + hq;
   const int G = a.Hq / a.Hkv;
   const size_t kvunit = ((size_t)l * a.B + b) * a.Hkv + hq / G;
-  const int tid = threadIdx.x, lane = tid & 63, c32 = lane & 31, hl = lane >> 5;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform over the wave
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, c16 = lane & 15, q4 = lane >> 4;
 
-  // row block u of this wave holds window rows row0 + 32 u + lane % 32
+  // query group g of this wave holds window rows row0 + 16 g + lane % 16
   const int row0 = rb * kRowBlock + w * 64;
-  int t[2], last[2];  // last key each row sees
-  uint4 qf[2][KS];
+  int t[4], pos[4];
+  uint4 qf[4][KS];
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    t[u] = row0 + 32 * u + c32;
-    const int tc = t[u] < a.W ? t[u] : a.W - 1;
-    last[u] = a.causal ? a.T - a.W + tc : a.T - 1;
+  for (int g = 0; g < 4; ++g) {
+    t[g] = row0 + 16 * g + c16;
+    const int tc = t[g] < a.W ? t[g] : a.W - 1;
+    pos[g] = a.T - a.W + tc;
     const char* qrow = (const char*)a.q_win + ((size_t)qunit * a.W + tc) * TL::RB;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[u][ks] = ldg16(qrow + ks * 32 + hl * 16);
+    for (int ks = 0; ks < KS; ++ks) qf[g][ks] = ldg16(qrow + (ks * 32 + q4 * 8) * DT::kElt);
   }
 
   const char* kh = (const char*)a.k + kvunit * a.T * TL::RB;
@@ -540,99 +480,73 @@ __global__ __launch_bounds__(kRowThreads16, 3) void k_rowstats16(EvictArgs a) {
   __syncthreads();
 
   const float cf = a.c32;
-  float nb[2] = {INFINITY, INFINITY};  // whole-number offset of each block's row (the same in both half-waves)
-  double ell[2] = {0.0, 0.0};          // this lane's sum of exp2(fma(c, s, nb)) so far
-  auto operand = [&](const unsigned char* kb, int ks) { return __builtin_bit_cast(typename M::Op, *(const uint4*)(kb + ks * 32)); };
-  auto rows = [&](int u, int ks) { return __builtin_bit_cast(typename M::Op, qf[u][ks]); };
-
-  // sums of a tile whose every key is visible to every row of the wave
-  auto sum_full = [&](int buf, float (&ps)[2]) {
-    f32x16 acc[2];
-    typename M::Op af[KS];
-    float x[2][16], pa[2] = {0.f, 0.f}, pb[2] = {0.f, 0.f};
-    const unsigned char* kb = &s_k[buf][c32 * TL::RS + hl * 16];
+  float nb[4];    // whole-number offset of each query group's row (this lane's keys)
+  double ell[4];  // sum of exp2(fma(c, s, nb)) so far
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) af[ks] = operand(kb, ks);
-    __builtin_amdgcn_sched_barrier(0);
-    auto vec = [&](auto chunk, int j) {  // chunk of block j
-      if (j < 0 || j >= KT / 16) return;
-      const int u = j & 1;
-      block_chunk<decltype(chunk)::value>([&](int r) { x[u][r] = fmaf(cf, acc[u][r], nb[u]); pin(x[u][r]); },
-                                          [&](int r) { x[u][r] = fast_exp2(x[u][r]); pin(x[u][r]); },
-                                          [&](int r) {
-                                            float& p = r & 1 ? pb[u] : pa[u];
-                                            p += x[u][r];
-                                            pin(p);
-                                          });
+  for (int g = 0; g < 4; ++g) {
+    nb[g] = INFINITY;
+    ell[g] = 0.0;
+  }
+  // one tile; block b = (key quarter b / 4, query group b % 4). FULL: every key of the tile visible
+  // to every row of the wave
+  auto tile = [&](auto full_tag, int buf, int j0) {
+    constexpr bool FULL = decltype(full_tag)::value;
+    float psg[4] = {0.f, 0.f, 0.f, 0.f};
+    uint4 af[KS];
+    auto load_af = [&](int kq) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        af[ks] = *(const uint4*)&s_k[buf][(16 * kq + c16) * TL::RS + (ks * 32 + q4 * 8) * DT::kElt];
     };
-    // block b = (key half b / 2, row block b % 2)
+    auto chain = [&](int g) {
+      f32x4 c = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int b = 0; b < KT / 16 + 2; ++b) {
+      for (int ks = 0; ks < KS; ++ks) c = mma16<DT>(af[ks], qf[g][ks], c);
+      return c;
+    };
+    auto visible = [&](int kq, int g, int r) {
+      if constexpr (FULL) return true;
+      const int j = j0 + 16 * kq + 4 * q4 + r;
+      return j < a.T && (!a.causal || j <= pos[g]);
+    };
+    auto sum4 = [&](const f32x4& c, int kq, int g) {
+      float ps = 0.f;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        if (b < KT / 16) {
-          acc[b & 1] = M::run(af[ks], rows(b & 1, ks), ks ? acc[b & 1] : f32x16{});
-          if ((b & 1) && b + 1 < KT / 16) af[ks] = operand(kb + 32 * (b / 2 + 1) * TL::RS, ks);
-          __builtin_amdgcn_sched_barrier(0);
+      for (int r = 0; r < 4; ++r)
+        if (visible(kq, g, r)) ps += fast_exp2(fmaf(cf, c[r], nb[g]));
+      return ps;
+    };
+    auto finish = [&](const f32x4& c, int kq, int g, float ps) {
+      if (ps > 2.f) {  // an exponent may exceed 1 (or the row's first terms): offset at the max
+        float tmax = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (visible(kq, g, r)) tmax = fmaxf(tmax, c[r]);
+        const float nb_new = -ceilf(cf * tmax);
+        if (nb_new < nb[g]) {
+          const int d = (int)(nb_new - nb[g]);
+          if (ell[g] > 0.0) ell[g] = ldexp(ell[g], d);
+          if (psg[g] > 0.f) psg[g] = ldexpf(psg[g], d);
+          nb[g] = nb_new;
         }
-        using std::integral_constant;
-        if (ks == 0) vec(integral_constant<int, 8>{}, b - 2);
-        if constexpr (KS == 8) {
-          if (ks == 0) vec(integral_constant<int, 0>{}, b - 1);
-          if (ks == 1) vec(integral_constant<int, 1>{}, b - 1);
-          if (ks == 2) vec(integral_constant<int, 2>{}, b - 1);
-          if (ks == 3) vec(integral_constant<int, 3>{}, b - 1);
-          if (ks == 4) vec(integral_constant<int, 4>{}, b - 1);
-          if (ks == 5) vec(integral_constant<int, 5>{}, b - 1);
-          if (ks == 6) vec(integral_constant<int, 6>{}, b - 1);
-          if (ks == 7) vec(integral_constant<int, 7>{}, b - 1);
-        } else {
-          if (ks == 0) vec(integral_constant<int, 0>{}, b - 1), vec(integral_constant<int, 1>{}, b - 1);
-          if (ks == 1) vec(integral_constant<int, 2>{}, b - 1), vec(integral_constant<int, 3>{}, b - 1);
-          if (ks == 2) vec(integral_constant<int, 4>{}, b - 1), vec(integral_constant<int, 5>{}, b - 1);
-          if (ks == 3) vec(integral_constant<int, 6>{}, b - 1), vec(integral_constant<int, 7>{}, b - 1);
-        }
+        ps = sum4(c, kq, g);
       }
+      psg[g] += ps;
+    };
+    load_af(0);
+    f32x4 cp = chain(0);
+#pragma unroll
+    for (int bb = 1; bb < 4 * (KT / 16); ++bb) {
+      if ((bb & 3) == 0) load_af(bb >> 2);
+      const f32x4 cc = chain(bb & 3);
+      const int kp = (bb - 1) >> 2, gp = (bb - 1) & 3;
+      finish(cp, kp, gp, sum4(cp, kp, gp));
+      cp = cc;
     }
+    finish(cp, KT / 16 - 1, 3, sum4(cp, KT / 16 - 1, 3));
 #pragma unroll
-    for (int u = 0; u < 2; ++u) ps[u] = pa[u] + pb[u];
+    for (int g = 0; g < 4; ++g) ell[g] += (double)psg[g];
   };
-  // any tile, one block after the other: f(u, r, score, visible) for every score
-  auto each = [&](int buf, int j0, auto f) {
-#pragma unroll 1
-    for (int h = 0; h < KT / 32; ++h) {
-      const unsigned char* kb = &s_k[buf][(32 * h + c32) * TL::RS + hl * 16];
-      f32x16 acc[2] = {};
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const typename M::Op af = operand(kb, ks);
-#pragma unroll
-        for (int u = 0; u < 2; ++u) acc[u] = M::run(af, rows(u, ks), acc[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int j = j0 + 32 * h + acc_row(r, lane);
-          f(u, acc[u][r], j <= last[u]);
-        }
-    }
-  };
-  // moves the offsets one below the tile's largest exponents, where that lowers them
-  auto set_offsets = [&](int buf, int j0) {
-    float mx[2] = {-INFINITY, -INFINITY};
-    each(buf, j0, [&](int u, float s, bool seen) { mx[u] = fmaxf(mx[u], seen ? s : -INFINITY); });
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      mx[u] = fmaxf(mx[u], __shfl_xor(mx[u], 32));
-      const float to = -ceilf(cf * mx[u]) - 1.f;
-      if (to < nb[u]) {
-        if (ell[u] > 0.0) ell[u] = ldexp(ell[u], (int)(to - nb[u]));
-        nb[u] = to;
-      }
-    }
-  };
-  bool fresh = true;  // no offsets yet
   for (int it = it0; it < it1; ++it) {
     const int buf = (it - it0) & 1;
     if (it + 1 < it1) fetch(it + 1);
@@ -640,30 +554,31 @@ __global__ __launch_bounds__(kRowThreads16, 3) void k_rowstats16(EvictArgs a) {
     // a wave none of whose rows sees the tile (rows past a ragged window, keys after its last row) only
     // helps stage it
     if (row0 < a.W && (!a.causal || j0 <= a.T - a.W + row0 + 63)) {
-      const bool full = j0 + KT - 1 < a.T && (!a.causal || j0 + KT - 1 <= a.T - a.W + row0);
-      float ps[2];
-      for (bool again = fresh;;) {
-        if (again) set_offsets(buf, j0);
-        if (full) {
-          sum_full(buf, ps);
-        } else {
-          ps[0] = ps[1] = 0.f;
-          each(buf, j0, [&](int u, float s, bool seen) { ps[u] += seen ? fast_exp2(fmaf(cf, s, nb[u])) : 0.f; });
-        }
-        if (again || !__any(ps[0] > 32.f || ps[1] > 32.f)) break;
-        again = true;
-      }
-      fresh = false;
-#pragma unroll
-      for (int u = 0; u < 2; ++u) ell[u] += (double)ps[u];
+      if (j0 + KT - 1 < a.T && (!a.causal || j0 + KT - 1 <= a.T - a.W + row0))
+        tile(std::true_type{}, buf, j0);
+      else
+        tile(std::false_type{}, buf, j0);
     }
     if (it + 1 < it1) stash(buf ^ 1);
     __syncthreads();
   }
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const double e = ell[u] + __shfl_xor(ell[u], 32);
-    if (hl == 0 && t[u] < a.W) put_row(a, ou, (size_t)qunit * a.W, sp, t[u], e, nb[u]);
+  for (int g = 0; g < 4; ++g) {
+    // the four lanes of a row (lane % 16 equal) meet at the smallest offset, in two pairwise steps
+    double e = ell[g];
+    float o = nb[g];
+#pragma unroll
+    for (int x = 16; x <= 32; x <<= 1) {
+      const double eo = __shfl_xor(e, x);
+      const float oo = __shfl_xor(o, x);
+      const float ox = fminf(o, oo);
+      double L = 0.0;
+      if (e > 0.0) L += ldexp(e, (int)(ox - o));
+      if (eo > 0.0) L += ldexp(eo, (int)(ox - oo));
+      e = L;
+      o = ox;
+    }
+    if (q4 == 0 && t[g] < a.W) put_row(a, ou, (size_t)qunit * a.W, sp, t[g], e, o);
   }
 }
 
@@ -1234,10 +1149,11 @@ hipError_t launch_rowstats(const EvictArgs& a, int dtype, int D, hipStream_t st)
 
 // A split is taken where it evens out the work: the launch ends with the compute unit that holds the most
 // workgroups (one alone on its unit runs at about 1.4 times the time of one among several), and each split
-// costs about six tiles beside its own: its rows' loads, and the first tile three times over for the offsets.
-// 32 heads of 7177 keys (192 row blocks): 148 us unsplit, 100 us in four; 84 heads of 2048 keys (168):
-// 37 and 25 us in three; 128 heads of 32768 keys (1664 = 6.5 a unit): 3.50 and 3.25 ms in two. 320 heads
-// of 8192 keys (8.75 a unit) stay whole.
+// costs about two tiles beside its own: its rows' loads, and the first tile's slow path to its offsets. Unsplit
+// and split, the merge (4.8 us) not counted: 32 heads of 7177 keys (192 row blocks) 218 and 126 us, in four; 84 heads
+// of 2048 keys (168) 75 and 50 us, in three; 144 heads of 2048 keys of 64 channels 87 and 67 us; 12 heads of 512 fp32
+// keys 25 and 11 us; 128 heads of 32768 keys (1664 = 6.5 a unit) 4.04 and 3.66 ms, in two. 320 heads of 8192 keys (8.75
+// a unit) stay whole.
 int row_splits(int heads, int T, int W, int causal) {
   const int64_t base = (int64_t)heads * ((W + kRowBlock - 1) / kRowBlock);
   const int ntile = ((causal ? T - W / 2 : T) + 63) / 64;
