@@ -135,6 +135,8 @@ size_t mpc_workspace_bytes(int32_t op, const mpc_dims* dims, int32_t T_or_Ts, co
  * Accumulation: fp32 matrix-core dot products; each exponent is one fp32 fused multiply-add
  * against a per-row whole-number offset that keeps every exponent at most 1, shared by the row sum
  * and the column sums; sums of at most 16 terms in fp32, accumulated across tiles in fp64.
+ * A row that sees a NaN score is NaN (its log-sum-exp and what it adds to every token it sees); a
+ * score of -infinity has weight zero.
  * token_score matches the exact (fp64) scores within a relative 2e-5 (the bound the tests hold it
  * to; the largest error measured over every token of the tested cases is 1.8e-6, and 3.3e-7 to
  * 7.3e-7 at the 8K-32K workloads, where tokens near the keep boundary are within 3e-7, as they are

@@ -135,6 +135,16 @@ struct TileChunks {
 constexpr int kWaves32 = 8, kFewWaves32 = 2;
 static_assert(kRowBlock == kColBlockKeys && kRowBlock == 32 * kWaves32, "both passes cover 256 rows / keys");
 
+// A row's offset before its first score: every term is then infinite, so that the offset moves, but a score of
+// -infinity already adds nothing.
+constexpr float kNoOffset = 3.4028234664e38f;
+
+// Part of a row's sum moved to a smaller offset (exact). A part without terms stays zero and NaN, which a NaN score
+// leaves, stays NaN, so that a row that sees one is NaN however its keys are divided over lanes and workgroups.
+__device__ __forceinline__ double moved(double sum, double from, double to) {
+  return sum > 0.0 ? ldexp(sum, (int)(to - from)) : sum;
+}
+
 // A window row's statistics: offset o and sum L of exp2(fma(c, s, o)) over its visible keys.
 __device__ __forceinline__ void put_stat(const EvictArgs& a, size_t row, double L, float o) {
   a.rowstat[row] = make_float2(o, (float)(1.0 / L));
@@ -222,7 +232,7 @@ __global__ __launch_bounds__(kWaves32* kWave) void k_rowstats(EvictArgs a) {
   __syncthreads();
 
   const float cf = a.c32;
-  float m = -INFINITY, nb = INFINITY;  // running max and its whole-number offset -ceil(c * m)
+  float m = -INFINITY, nb = kNoOffset;  // running max and its whole-number offset -ceil(c * m)
   double ell = 0.0;                    // sum of exp2(fma(c, s, nb)) so far
   for (int it = it0; it < it1; ++it) {
     const int buf = (it - it0) & 1;
@@ -272,9 +282,7 @@ __global__ __launch_bounds__(kWaves32* kWave) void k_rowstats(EvictArgs a) {
   const double eo = __shfl_xor(ell, 32);
   const float nbo = __shfl_xor(nb, 32);
   const float nbx = fminf(nb, nbo);
-  double L = 0.0;
-  if (ell > 0.0) L += ldexp(ell, (int)(nbx - nb));
-  if (eo > 0.0) L += ldexp(eo, (int)(nbx - nbo));
+  const double L = moved(ell, nb, nbx) + moved(eo, nbo, nbx);
   if (hl == 0 && t < a.W) put_row(a, ou, (size_t)qunit * a.W, sp, t, L, nbx);
 }
 
@@ -484,7 +492,7 @@ __global__ __launch_bounds__(kRowThreads16, 3) void k_rowstats16(EvictArgs a) {
   double ell[4];  // sum of exp2(fma(c, s, nb)) so far
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
-    nb[g] = INFINITY;
+    nb[g] = kNoOffset;
     ell[g] = 0.0;
   }
   // one tile; block b = (key quarter b / 4, query group b % 4). FULL: every key of the tile visible
@@ -572,10 +580,7 @@ __global__ __launch_bounds__(kRowThreads16, 3) void k_rowstats16(EvictArgs a) {
       const double eo = __shfl_xor(e, x);
       const float oo = __shfl_xor(o, x);
       const float ox = fminf(o, oo);
-      double L = 0.0;
-      if (e > 0.0) L += ldexp(e, (int)(ox - o));
-      if (eo > 0.0) L += ldexp(eo, (int)(ox - oo));
-      e = L;
+      e = moved(e, o, ox) + moved(eo, oo, ox);
       o = ox;
     }
     if (q4 == 0 && t[g] < a.W) put_row(a, ou, (size_t)qunit * a.W, sp, t[g], e, o);
@@ -585,7 +590,7 @@ __global__ __launch_bounds__(kRowThreads16, 3) void k_rowstats16(EvictArgs a) {
 constexpr int kMergeThreads = 64;
 
 // Statistics of the window rows whose keys were split over several workgroups: the splits' sums meet at the
-// smallest offset. A split none of whose keys the row sees holds a zero sum at an infinite offset. Bound by
+// smallest offset. A split none of whose keys the row sees holds a zero sum at kNoOffset. Bound by
 // latency: one memory round trip for all splits (12 heads of 102 rows in eight splits: 5.7 -> 4.5 us).
 __global__ __launch_bounds__(kMergeThreads) void k_rowmerge(EvictArgs a) {
   const int64_t n = (int64_t)a.own.n * a.B * a.Hq * a.W, i = (int64_t)blockIdx.x * kMergeThreads + threadIdx.x;
@@ -599,8 +604,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_rowmerge(EvictArgs a) {
 #pragma unroll
   for (int s = 0; s < kMaxRowSplits; ++s) o = fmin(o, x[s].y);
 #pragma unroll
-  for (int s = 0; s < kMaxRowSplits; ++s)
-    if (x[s].x > 0.0) L += ldexp(x[s].x, (int)(o - x[s].y));
+  for (int s = 0; s < kMaxRowSplits; ++s) L += moved(x[s].x, x[s].y, o);
   const size_t unit = (size_t)a.own.local(ou / (a.B * a.Hq)) * a.B * a.Hq + ou % (a.B * a.Hq);
   put_stat(a, unit * a.W + t, L, (float)o);
 }

@@ -1,6 +1,9 @@
 """Rounding of the 16-bit row pass where it can be told apart: how many terms are summed in fp32, and how far a term's
-exponent may lie from the row's offset. Log-sum-exps near zero, so that their own rounding does not hide it.
+exponent may lie from the row's offset. Log-sum-exps near zero, so that their own rounding does not hide it. Then scores
+that are not finite, in every form of the row pass.
 """
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -73,3 +76,33 @@ def test_exponents_stay_at_most_one(dtype):
     rms = float(np.sqrt((err**2).mean()))
     say(f"  rms error {rms:.2e}, largest {np.abs(err).max():.2e}")
     assert rms <= 5.5e-8
+
+
+@pytest.mark.parametrize("heads,T,W", [(2, 1025, 150), (512, 200, 40)], ids=["split", "whole"])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16, torch.float32], ids=str)
+def test_rows_that_see_a_nan_are_nan_and_minus_infinity_adds_nothing(heads, T, W, dtype):
+    """A NaN key makes every row that sees it NaN, wherever its tile, lane or workgroup, and leaves the others alone; a
+    score of -infinity, at the start of a row or later, has weight zero."""
+    import paper_2501_06807_amd as M
+    say(f"[not finite] heads={heads} T={T} W={W} {dtype}")
+    gen = torch.Generator().manual_seed(5)
+    q = torch.randn((1, 1, heads, W, D), generator=gen).to(dtype)
+    q[..., 0] = q[..., 0].abs() + 0.5
+    k = torch.randn((1, 1, heads, T, D), generator=gen).to(dtype)
+    sm = 1 / math.sqrt(D)
+    for kind, keys in (("nan", [T - W // 2]), ("nan", [T - W // 2 + 7]), ("nan", [T - 1]), ("nan", [3]), ("-inf", [0]),
+                       ("-inf", list(range(40)) + [T - W, T - 2])):
+        kk = k.clone()
+        kk[..., keys, 0] = float(kind)
+        s = (q[0, 0].double() @ kk[0, 0].double().transpose(1, 2)) * float(np.float32(sm))
+        seen = torch.arange(T)[None, :] <= torch.arange(W)[:, None] + T - W
+        want = torch.logsumexp(s.masked_fill(~seen, -math.inf), -1)
+        qt, kt = q.cuda(), kk.cuda()
+        kept = torch.zeros((1, 1, heads, 1), dtype=torch.int32, device="cuda")
+        out = torch.empty((1, 1, heads, 1, D), dtype=dtype, device="cuda")
+        lse = torch.zeros((1, 1, heads, W), dtype=torch.float32, device="cuda")
+        M.mpc_static_evict(qt, kt, kt, kept, out, torch.empty_like(out), keep=1, local_keep=0, sm_scale=sm, causal=True,
+                           row_lse=lse)
+        torch.cuda.synchronize()
+        # the eviction tests' bound on log-sum-exps of such scores
+        torch.testing.assert_close(lse[0, 0].double().cpu(), want, rtol=0, atol=6e-6, equal_nan=True, msg=lambda m: f"{kind} {keys[:3]}: {m}")
