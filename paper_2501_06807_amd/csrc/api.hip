@@ -496,6 +496,42 @@ mpc_status prepare_decode(const mpc_dims* dims, int32_t Ts, int32_t n_tail, int3
   return MPC_OK;
 }
 
+// One decode step: its arguments but for the workspace's, and how it runs.
+enum StepForm { kTwoKernels, kSelfSelecting, kClaiming };
+struct Step {
+  mpc::FusedArgs f{};
+  mpc::DecodePlan plan{};
+  mpc::FusedPlan fp{};
+  StepForm form;
+  bool per_q_head;
+  int units = 0, G = 0;
+};
+mpc_status prepare_step(const mpc_dims* dims, int32_t Ts, int32_t n_tail, const mpc_select_cfg* cfg, const void* q,
+                        const float* cent, const float* scent, const void* k_cache, const void* v_cache, float sm_scale,
+                        int32_t* sel, float* sel_score, void* out, float* lse, Step* p) {
+  mpc::SelectArgs& sa = p->f.s;
+  mpc::DecodeArgs& da = p->f.d;
+  mpc_status s = prepare_select(dims, Ts, cfg, q, cent, scent, sel, sel_score, &sa);
+  if (s != MPC_OK) return s;
+  s = prepare_decode(dims, Ts, n_tail, cfg->cluster_size, q, k_cache, v_cache, sel, sa.Hsel, cfg->k_clusters,
+                     sm_scale, out, lse, &da, &p->plan, &p->units, &p->G);
+  if (s != MPC_OK) return s;
+  p->per_q_head = sa.Hsel != dims->n_kv_heads;
+  p->fp = mpc::fused_plan(sa, dims->head_dim, p->plan.splits);
+  // The claiming launch trails the two kernels the more units wait for a selection and the shorter their lists
+  // are, since every unit's attention then stands behind one (us, one launch and two: 1024 units of 384 rows 50.7
+  // and 38.8, 288 of 128 13.2 and 10.5, 512 of 48 15.9 and 11.3). It keeps the blocks whose workgroups are all
+  // resident at once and have 64 KiB of K rows each, where it is within a tenth (512 of 384 rows 25.7 and 24.2, of 480
+  // 34.1 and 34.5) and a caller gets the one launch that this entry point is for.
+  const bool claim = !p->per_q_head && p->plan.splits == 1 && p->plan.waves > 1 && p->units <= 2 * mpc::kNumCU &&
+                     (int64_t)da.k_sel * da.s * dims->head_dim * elt_size(dims->dtype) >= (64 << 10);
+  p->form = !mpc::fused_fits(p->fp, dims->head_dim, p->G) ? kTwoKernels
+            : p->fp.self                                  ? kSelfSelecting
+            : claim                                       ? kClaiming
+                                                          : kTwoKernels;
+  return MPC_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -545,51 +581,48 @@ mpc_status mpc_decode_step(const mpc_dims* dims, int32_t Ts, int32_t n_tail, con
                            const void* k_cache, const void* v_cache, float sm_scale, int32_t* sel,
                            float* sel_score, void* out, float* lse, void* ws, size_t ws_bytes,
                            void* stream) {
-  mpc::SelectArgs sa{};
-  mpc_status s = prepare_select(dims, Ts, cfg, q, cent, scent, sel, sel_score, &sa);
-  if (s != MPC_OK) return s;
-  mpc::DecodeArgs da{};
-  mpc::DecodePlan plan{};
-  int units = 0, G = 0;
-  s = prepare_decode(dims, Ts, n_tail, cfg->cluster_size, q, k_cache, v_cache, sel, sa.Hsel, cfg->k_clusters,
-                     sm_scale, out, lse, &da, &plan, &units, &G);
+  Step p;
+  mpc_status s = prepare_step(dims, Ts, n_tail, cfg, q, cent, scent, k_cache, v_cache, sm_scale, sel, sel_score, out, lse, &p);
   if (s != MPC_OK) return s;
   const StepWs lay = step_ws(dims, cfg);
   if (!ws || ws_bytes < lay.total)
     return fail(MPC_EWORKSPACE, "decode step needs %zu workspace bytes", lay.total);
-  const bool per_q_head = sa.Hsel != dims->n_kv_heads;
   hipStream_t st = (hipStream_t)stream;
   clear_stale_error();
-  const mpc::FusedPlan fp = mpc::fused_plan(sa, dims->head_dim, plan.splits);
-  if (plan.splits > 1) {
-    da.part = (float*)((char*)ws + lay.part);
-    da.cnt = (int*)((char*)ws + lay.part + decode_ws(dims, per_q_head).cnt);
+  mpc::FusedArgs& f = p.f;
+  if (p.plan.splits > 1) {
+    f.d.part = (float*)((char*)ws + lay.part);
+    f.d.cnt = (int*)((char*)ws + lay.part + decode_ws(dims, p.per_q_head).cnt);
   }
-  // The claiming launch trails the two kernels the more units wait for a selection and the shorter their lists
-  // are, since every unit's attention then stands behind one (us, one launch and two: 1024 units of 384 rows 50.7
-  // and 38.8, 288 of 128 13.2 and 10.5, 512 of 48 15.9 and 11.3). It keeps the blocks whose workgroups are all
-  // resident at once and have 64 KiB of K rows each, where it is within a tenth (512 of 384 rows 25.7 and 24.2, of 480
-  // 34.1 and 34.5) and a caller gets the one launch that this entry point is for.
-  const bool claim = !per_q_head && plan.splits == 1 && plan.waves > 1 && units <= 2 * mpc::kNumCU &&
-                     (int64_t)da.k_sel * da.s * dims->head_dim * elt_size(dims->dtype) >= (64 << 10);
-  if (!(fp.self || claim) || !mpc::fused_fits(fp, dims->head_dim, G)) {
-    // two kernels in sequence
-    if (sa.own.n > 0 &&
-        (s = launched(mpc::launch_select(sa, dims->dtype, dims->head_dim, st), "select")) != MPC_OK)
+  if (p.form == kTwoKernels) {
+    if (f.s.own.n > 0 &&
+        (s = launched(mpc::launch_select(f.s, dims->dtype, dims->head_dim, st), "select")) != MPC_OK)
       return s;
-    if ((s = launched(mpc::launch_sparse_decode(da, dims->dtype, dims->head_dim, G, units, plan, st),
+    if ((s = launched(mpc::launch_sparse_decode(f.d, dims->dtype, dims->head_dim, p.G, p.units, p.plan, st),
                       "sparse decode attention")) != MPC_OK)
       return s;
     return ok();
   }
-  mpc::FusedArgs f{};
-  f.s = sa;
-  f.d = da;
   f.sync = (mpc::FusedSync*)ws;
   f.state = (int*)((char*)ws + lay.state);
   f.cons = (int*)((char*)ws + lay.cons);
-  if ((s = launched(mpc::launch_decode_step(f, fp, dims->dtype, dims->head_dim, G, st), "decode step")) != MPC_OK)
+  if ((s = launched(mpc::launch_decode_step(f, p.fp, dims->dtype, dims->head_dim, p.G, st), "decode step")) != MPC_OK)
     return s;
+  return ok();
+}
+
+// Not part of the interface: how mpc_decode_step runs these sizes, for the tests to state which kernels they reach.
+// form: 0 two kernels, 1 self-selecting launch, 2 claiming launch; splits and waves of the attention plan.
+mpc_status mpc_test_step_form(const mpc_dims* dims, int32_t Ts, int32_t n_tail, const mpc_select_cfg* cfg, int32_t* form,
+                              int32_t* splits, int32_t* waves) {
+  void* any = (void*)256;  // the preparation only checks that pointers are there and aligned
+  Step p;
+  const mpc_status s = prepare_step(dims, Ts, n_tail, cfg, any, (const float*)any, (const float*)any, any, any, 1.f,
+                                    (int32_t*)any, nullptr, any, nullptr, &p);
+  if (s != MPC_OK) return s;
+  *form = p.form;
+  *splits = p.plan.splits;
+  *waves = p.plan.waves;
   return ok();
 }
 

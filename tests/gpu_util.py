@@ -73,3 +73,18 @@ def random_sel(rng, n_units, C, k, include_last=True):
             s = rng.choice(C, k, replace=False)
         sel[u] = np.sort(s)
     return sel
+
+
+FORMS = ("two kernels", "self-selecting", "claiming")
+
+
+def step_form(dims, Ts, cfg, n_tail=0):
+    """How mpc_decode_step runs these sizes: (one of FORMS, attention splits, waves per unit). No GPU needed."""
+    import ctypes
+
+    from paper_2501_06807_amd import _lib as L
+    form, splits, waves = (ctypes.c_int32() for _ in range(3))
+    s = L.lib().mpc_test_step_form(ctypes.byref(dims), Ts, n_tail, ctypes.byref(cfg), ctypes.byref(form),
+                                   ctypes.byref(splits), ctypes.byref(waves))
+    assert s == 0, L.lib().mpc_last_error()
+    return FORMS[form.value], splits.value, waves.value

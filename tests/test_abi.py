@@ -238,6 +238,32 @@ def test_prefill_validation():
     assert call(ctypes.byref(bad_keep), ctypes.byref(good)) == L.MPC_ESHAPE
 
 
+def test_decode_step_forms():
+    """Which form a decode step takes, on both sides of each limit of the rule."""
+    from gpu_util import step_form
+
+    def form(units, rows, dtype=2, group="sum", G=1, d=128):
+        dims = _dims(n_layers=units, n_q_heads=G, n_kv_heads=1, head_dim=d, dtype=dtype) if units <= 256 else \
+            _dims(n_layers=units // 8, n_q_heads=8 * G, n_kv_heads=8, head_dim=d, dtype=dtype)
+        cfg = L.select_cfg(16, 4, 32, rows // 16, share_period=1, group=group)
+        return step_form(dims, 2048, cfg)
+
+    assert form(256, 1024) == ("self-selecting", 1, 8)
+    assert form(128, 512) == ("self-selecting", 2, 8)      # 256 workgroups
+    assert form(136, 512) == ("two kernels", 2, 8)         # 272
+    assert form(86, 768) == ("two kernels", 3, 8)          # 258
+    assert form(264, 256) == ("claiming", 1, 8)            # 64 KiB a list
+    assert form(264, 240) == ("two kernels", 1, 8)
+    assert form(512, 256) == ("claiming", 1, 8)
+    assert form(520, 256) == ("two kernels", 1, 8)
+    assert form(264, 512, d=64) == ("claiming", 1, 8)
+    assert form(264, 496, d=64) == ("two kernels", 1, 8)
+    assert form(264, 128, dtype=0) == ("claiming", 1, 8)
+    assert form(264, 256, G=2, group="head") == ("two kernels", 1, 8)
+    assert form(1024, 64) == ("two kernels", 1, 1)         # a wave per list of at most 16 KiB
+    assert form(1024, 80) == ("two kernels", 1, 8)
+
+
 def test_status_strings():
     lib = L.lib()
     for s in range(6):

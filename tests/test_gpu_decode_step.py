@@ -2,11 +2,13 @@
 
 The step must give bit for bit what mpc_select_clusters followed by mpc_sparse_decode_attn give,
 and both are checked against the oracle: the selection with the tie rule, the attention output
-recomputed by the oracle from the selection the GPU made. Cases are chosen so that both one-launch
-kernels run: the self-selecting one (at most one (layer, sequence, kv head) unit per compute unit:
-every workgroup computes its owner head's selection) and the claiming one (more units: the first
-consumer of an owner head selects, the others wait for it), with per-head and per-wave selection,
-owners inside and before the block, and the sequential fallback of small blocks.
+recomputed by the oracle from the selection the GPU made. Cases are chosen so that every form runs
+(FORM states which): the self-selecting launch (at most one attention workgroup per compute unit:
+each computes its owner head's selection), the claiming one (up to two units per compute unit with
+long lists: the first consumer of an owner head selects, the others wait for it; its other variants
+are in test_gpu_decode_claim.py), and the two kernels in sequence behind the same entry point (which
+the comparison with the two calls then only checks for its arguments), with owners inside and before
+the block.
 """
 import math
 
@@ -16,7 +18,7 @@ import torch
 
 import oracle
 import synth
-from gpu_util import assert_out_close, bits_to_torch, random_sel, say, to_f64
+from gpu_util import assert_out_close, bits_to_torch, random_sel, say, step_form, to_f64
 from test_gpu_decode import _check_selection
 
 pytestmark = pytest.mark.gpu
@@ -29,11 +31,11 @@ CASES = {
     "C3-L16": ("C3", dict(n_layers=16), 0),
     # layers 3..10: layers 3-5 are owned by layer 2 (before the block) -> their selection is an input
     "C3-L8@3": ("C3", dict(n_layers=8), 3),
-    # 512 owner heads -> one wave per head
+    # 1024 units, 512 owner heads -> one wave per head
     "C4-L8": ("C4", dict(n_layers=8, keep=2048, k_super=4, k_clusters=8), 0),
     # GQA group 4, 32 layers x 8 kv heads = 256 units
     "C5-L32": ("C5", dict(keep=8192, k_super=8), 0),
-    # small blocks: the two kernels in sequence
+    # small blocks with short lists, unsplit
     "C1": ("C1", dict(), 0),
     "C2": ("C2", dict(), 0),
     # the other similarity measures in one launch (four heads per group for the bound)
@@ -48,10 +50,13 @@ CASES = {
     "C2-one-cluster": ("C2", dict(keep=10, k_super=1, k_clusters=1), 0),
     "C2-all-selected": ("C2", dict(n_layers=32, n_q_heads=8, n_kv_heads=8, keep=512, k_super=8, k_clusters=32), 0),
     # the most layers one call takes (256): one kv head -> 256 units (self-selecting); two kv heads
-    # from layer 5 -> 512 units (claiming), layer 5 owned by layer 4 before the block
+    # from layer 5 -> 512 units of 16 KiB lists (two kernels), layer 5 owned by layer 4 before the block
     "C2-L256": ("C2", dict(n_layers=256, n_q_heads=1, n_kv_heads=1, keep=512), 0),
     "C2-L256x2@5": ("C2", dict(n_layers=256, n_q_heads=2, n_kv_heads=2, keep=512), 5),
 }
+
+FORM = {c: "self-selecting" for c in CASES} | {"C3-L16": "claiming", "C4-L8": "two kernels", "X1-L8": "two kernels",
+                                               "C2-L256x2@5": "two kernels"}
 
 
 def _setup(case):
@@ -96,6 +101,7 @@ def test_decode_step_equals_two_calls_and_oracle(case):
     shape_out = (w.n_layers, w.batch, w.n_q_heads, w.head_dim)
     sm = 1.0 / math.sqrt(w.head_dim)
     dims = M.dims_of(torch.empty(shape_out, dtype=dt), kd, layer0)
+    assert step_form(dims, w.keep, cfg)[0] == FORM[case]
     ws = M.workspace(M.workspace_bytes(M.MPC_OP_DECODE_STEP, dims, w.keep, cfg), "cuda")
     ws_attn = M.workspace(M.workspace_bytes(M.MPC_OP_DECODE_ATTN, dims, w.keep), "cuda")
     # layers owned before the block arrive with a selection made upstream (here: random, ascending)

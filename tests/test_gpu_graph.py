@@ -5,18 +5,24 @@ import pytest
 import torch
 
 import synth
-from gpu_util import say
+from gpu_util import say, step_form
 
 pytestmark = pytest.mark.gpu
 
 CASES = {
-    # 144 units: the one-launch step takes the two kernels in turn, the attention split over workgroups
+    # 144 units of short lists: the self-selecting one-launch kernel, unsplit
     "C2": ("C2", {}),
-    # 256 units: the self-selecting one-launch kernel
+    # 256 units: the same, one per compute unit
     "C3-L8": ("C3", dict(n_layers=8)),
+    # 32 units in several splits: the same with split attention (its arrival counts back at zero after every launch)
+    "C3-L1-long": ("C3", dict(n_layers=1, k_clusters=40)),
+    # 128 units in three splits: the two kernels in turn, the attention split over workgroups
+    "C3-L4-long": ("C3", dict(n_layers=4, k_clusters=24)),
     # 512 units: the claiming one-launch kernel (its workspace words back at zero after every launch)
     "C3-L16": ("C3", dict(n_layers=16)),
 }
+FORM = {"C2": ("self-selecting", 1), "C3-L8": ("self-selecting", 1), "C3-L1-long": ("self-selecting", 5),
+        "C3-L4-long": ("two kernels", 3), "C3-L16": ("claiming", 1)}
 
 
 def _inputs(w, steps=3):
@@ -48,6 +54,7 @@ def test_decode_graph_replays_equal_eager(case, fused):
     say(f"[graph decode] {case} fused={fused} L={w.n_layers} Hkv={w.n_kv_heads} Ts={w.keep}")
     q_win, k, v, qs = _inputs(w)
     path = _path(w)
+    assert step_form(path._kvdims, w.keep, path.cfg)[:2] == FORM[case]
     path.prefill(q_win, k, v)
     step = path.decode_fused if fused else path.decode
     ref = []
