@@ -244,9 +244,11 @@ mpc_status mpc_sparse_decode_attn(const mpc_dims* dims, int32_t Ts, int32_t n_ta
  * reached (no such case is known: it would take a selection that never gets published), the unit
  * sets bit 0 of the error word and writes NaN to its out and lse rows instead of attending; the
  * call still returns MPC_OK, since the status covers only validation and launch.
- * Blocks of more attention workgroups than the chip holds at once, or of short lists on more of them than
- * compute units, and blocks whose selection and attention together need more LDS than one workgroup has, run
- * the two kernels one after the other instead (same results). */
+ * Which form runs: with a workgroup per attention unit, or per split of one, and at most 256 of them (one per
+ * compute unit), each selects for itself and none waits. Unsplit blocks of up to 512 units with at least 64 KiB
+ * of selected K rows each, not under MPC_GROUP_HEAD, take the launch described above, in which the first unit of a head
+ * selects. All other blocks, and those whose selection and attention together need more LDS than one workgroup has,
+ * run the two kernels one after the other (same results). */
 mpc_status mpc_decode_step(const mpc_dims* dims, int32_t Ts, int32_t n_tail, const mpc_select_cfg* cfg,
                            const void* q, const float* cent, const float* scent,
                            const void* k_cache, const void* v_cache, float sm_scale, int32_t* sel,
