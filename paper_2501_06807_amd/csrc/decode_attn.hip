@@ -106,7 +106,8 @@ DecodePlan decode_plan(int units, int n_slot, int s, int D, int elt, int G) {
   // merge of its waves. us per launch, workgroup and wave form: 8192 units of 48 rows of 256 B 54.7 and 34.4, of 64
   // rows 54.7 and 44.1, of 96 66.1 and 67.5, of 128 83.3 and 88.5; 4096 of 64 27.4 and 23.1; 8192 of 48 rows of
   // 128 B 46.6 and 19.8, of 128 53.6 and 43.1; 1024 of 48 rows of 256 B 9.3 and 9.3.
-  if (G <= 2 && p.splits == 1 && units >= 4 * kNumCU && n_slot * D * elt <= (16 << 10) && n_slot <= kMaxWaveList * s)
+  if (G <= 2 && p.splits == 1 && units >= 4 * kNumCU && (int64_t)n_slot * D * elt <= (16 << 10) &&
+      n_slot <= (int64_t)kMaxWaveList * s)
     p.waves = 1;
   return p;
 }

@@ -264,6 +264,15 @@ def test_decode_step_forms():
     assert form(1024, 80) == ("two kernels", 1, 8)
 
 
+def test_decode_plan_of_very_large_clusters():
+    """List sizes in bytes go past 32 bits: one cluster of 2^23 or 2^24 rows (cut off at the cached rows) is not a
+    short list, and gets a workgroup per unit."""
+    from gpu_util import step_form
+    for log2, dtype, d in ((23, 2, 128), (24, 2, 128), (23, 0, 128), (24, 1, 64), (25, 1, 64), (29, 1, 64)):
+        dims = _dims(n_layers=128, n_q_heads=8, n_kv_heads=8, head_dim=d, dtype=dtype)
+        assert step_form(dims, 1000, L.select_cfg(1 << log2, 1, 1, 1))[1:] == (1, 8), (log2, dtype, d)
+
+
 def test_status_strings():
     lib = L.lib()
     for s in range(6):
