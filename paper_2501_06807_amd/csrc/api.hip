@@ -80,11 +80,14 @@ constexpr size_t kScratchBytes = (size_t)32 << 20;  // static array of mpc_stati
 
 // Static eviction workspace: the (exponent offset, 1 / sum) pair of every window row, then fp32
 // token scores, then the column pass's partials. The row pass's partials take the place of both before (they are
-// merged by the time the column pass starts). The size is that of rows and scores, which grows with every dimension,
-// and a fixed room for partials, not what the splits of these sizes take: fewer keys may take more splits, and a
-// workspace made for the longest prompt has to serve the shorter ones. A block whose rows and scores fit the static
-// array of mpc_static_evict_noalloc stays inside it, so that no block is refused for its splits and both entry
-// points split alike. 16 MiB hold the splits of every block up to about 4000 row blocks of 256 rows.
+// merged by the time the column pass starts). The size is that of rows and scores and a room for partials: what the
+// most splits of these rows or keys take, up to a limit. Both grow with every dimension, which the splits themselves
+// do not: fewer keys may take more splits, and a workspace made for the longest prompt has to serve the
+// shorter ones. A block whose rows and scores fit the static array of mpc_static_evict_noalloc stays inside it, so that
+// no block is refused for its splits and both entry points split alike. A row block of 256 rows takes 4 KiB for each of
+// its parts, so the limit holds about 4000 of them; blocks that would take more are split into fewer parts than
+// row_splits asks for (12 heads of 111616 keys and 11161 window rows, 528 row blocks: ten instead of thirteen; 24
+// heads of 131072 keys and 26214 rows, 2472 row blocks: none instead of three).
 constexpr size_t kSplitRoom = (size_t)16 << 20;
 
 struct EvictWs {
@@ -97,7 +100,9 @@ EvictWs evict_ws(const mpc_dims* d, int T, const mpc_evict_cfg* cfg) {
   w.rowstat = 0;
   w.score = align256((size_t)d->n_layers * d->batch * d->n_q_heads * W * sizeof(double));
   w.col_part = w.score + align256((size_t)d->n_layers * d->batch * d->n_kv_heads * T * sizeof(float));
-  w.total = w.col_part + kSplitRoom;
+  const size_t all = (size_t)d->n_layers * d->batch;
+  w.total = w.col_part + std::min(kSplitRoom, align256(std::max(all * d->n_q_heads * W * sizeof(double2) * mpc::kMaxRowSplits,
+                                                                all * d->n_kv_heads * T * sizeof(double) * mpc::kMaxColSplits)));
   if (w.col_part <= kScratchBytes) w.total = std::min(w.total, kScratchBytes);
   const mpc::OwnerTable own = mpc::owner_table(d->layer0, d->n_layers, cfg->share_period, cfg->share_start);
   const size_t heads = (size_t)own.n * d->batch * d->n_q_heads, kv_heads = (size_t)own.n * d->batch * d->n_kv_heads;

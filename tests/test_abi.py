@@ -211,6 +211,16 @@ def test_evict_workspace_of_the_longest_prompt_serves_the_shorter_ones():
             assert grow == sorted(grow), (T, grow)
 
 
+def test_evict_workspace_of_small_blocks_is_small():
+    """The room for split passes is what sixteen splits of the block's rows or keys can take, not a fixed size."""
+    for n_layers, hq, hkv, T, W in ((1, 12, 12, 512, 102), (1, 2, 2, 64, 12), (1, 32, 8, 300, 60), (1, 2, 2, 3000, 600), (12, 12, 12, 64, 12)):
+        d = _dims(n_layers=n_layers, n_q_heads=hq, n_kv_heads=hkv)
+        cfg = L.MpcEvictCfg(window=W, keep=32, local_keep=32, sm_scale=0.088, causal=1, share_period=1, share_start=2)
+        base = n_layers * (hq * W * 8 + hkv * T * 4)
+        got = L.workspace_bytes(L.MPC_OP_STATIC_EVICT, d, T, cfg)
+        assert got <= base + 16 * n_layers * max(hq * W * 16, hkv * T * 8) + 512, (n_layers, hq, hkv, T, W, got)
+
+
 def test_prefill_validation():
     d = _dims(n_layers=4, batch=1, n_q_heads=8, n_kv_heads=2)
     ecfg = L.MpcEvictCfg(window=100, keep=200, local_keep=32, sm_scale=0.088, causal=1, share_period=2,
