@@ -98,21 +98,23 @@ __global__ __launch_bounds__(kFusedWaves* kWave) void k_decode_step(FusedArgs f)
 // launch would cost, about the gap between two kernels and the reread of query and list, is more than the
 // repeated selection as long as each workgroup has a compute unit to itself. One launch against two, us: 32
 // units of 384 rows, unsplit, 9.9 and 10.9; 32 of 1632 in six splits 13.2 and 14.2; 64 of 384 (fp32) in three
-// 11.9 and 13.0; 8 of 640 with four query heads in five 16.1 and 17.0.
+// 11.9 and 13.0; 8 of 640 with four query heads in five 16.1 and 17.0. Unsplit units take a kernel of their own without
+// the split's index arithmetic, stores and merge: 256 units of 640 rows, four query heads each, 24.73 us in the common kernel,
+// 24.47 us so (24.65 us before there was a split form).
 constexpr int kDies = 8;  // compute dies (XCDs); workgroup p of a launch runs on die p % kDies
 
 // Unit and split of workgroup p: ranks i of the owner-major order (all units of one owner head, then the next
 // head; a unit's splits one after the other) are dealt to the dies in contiguous runs, so the workgroups that
 // select alike share a die's L2. Returns -1 for the padding positions of the last run.
+template <bool SPLIT>
 __device__ __forceinline__ int self_unit(const SelectArgs& s, int splits, int p, int* split) {
+  if constexpr (!SPLIT) splits = 1;  // folds the arithmetic below
   const int BH = s.B * s.Hsel, n_items = s.n_layers * BH * splits;
   const int per = (n_items + kDies - 1) / kDies;
   int i = (p % kDies) * per + p / kDies;
   if (i >= n_items) return -1;
-  if (splits > 1) {
-    *split = i % splits;
-    i /= splits;
-  }
+  *split = i % splits;
+  i /= splits;
   // owner group of rank i: layers [lb, le) that share one selection (or, before the first owner
   // of the block, layers whose selection is an input); a group's ranks are [lb * BH, le * BH), so it
   // is the group of layer i / BH
@@ -123,33 +125,45 @@ __device__ __forceinline__ int self_unit(const SelectArgs& s, int splits, int p,
   return (lb + il % n) * BH + il / n;
 }
 
-template <class DT, int D, int G, bool MP, bool GMAX, bool STREAM_K>
+template <class DT, int D, int G, bool MP, bool GMAX, bool STREAM_K, bool SPLIT>
 __global__ __launch_bounds__(kFusedWaves* kWave) void k_decode_self(FusedArgs f) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int32_t s_pick[dev::kMaxSel];
   const SelectArgs& sa = f.s;
   int split = 0;
-  const int unit = self_unit(sa, f.d.splits, blockIdx.x, &split);  // (l * B + b) * Hsel + h
+  const int unit = self_unit<SPLIT>(sa, f.d.splits, blockIdx.x, &split);  // (l * B + b) * Hsel + h
   if (unit < 0) return;
   const int BH = sa.B * sa.Hsel, l = unit / BH;
+  if constexpr (!SPLIT) {
+    __builtin_assume(l >= 0);
+    __builtin_assume(f.d.splits == 1);
+  }
   const int o = sa.own.index_of(l);  // -1: owned before the block, its selection is an input
   if (o >= 0) {
     // the first split's workgroup writes the selection out
     dev::select_block<DT, D, kFusedWaves, false, 2, MP, true, GMAX>(sa, o * BH + unit % BH, smem, s_pick,
-                                                                    split == 0 ? l : -1);
+                                                                    SPLIT && split > 0 ? -1 : l);
     __syncthreads();
   }
   dev::attend<DT, D, G, kFusedWaves, 4, false, STREAM_K>(f.d, unit, split, o >= 0 ? s_pick : nullptr);
 }
 
-template <class DT, int D, int G, bool MP, bool GMAX>
-void launch_self(const FusedArgs& f, size_t smem, hipStream_t st) {
+template <class DT, int D, int G, bool MP, bool GMAX, bool SPLIT>
+void launch_self_split(const FusedArgs& f, size_t smem, hipStream_t st) {
   const int items = f.s.n_layers * f.s.B * f.s.Hsel * f.d.splits;
   const dim3 grid((items + kDies - 1) / kDies * kDies), block(kFusedWaves * kWave);
   if (f.d.stream_k)
-    hipLaunchKernelGGL((k_decode_self<DT, D, G, MP, GMAX, true>), grid, block, smem, st, f);
+    hipLaunchKernelGGL((k_decode_self<DT, D, G, MP, GMAX, true, SPLIT>), grid, block, smem, st, f);
   else
-    hipLaunchKernelGGL((k_decode_self<DT, D, G, MP, GMAX, false>), grid, block, smem, st, f);
+    hipLaunchKernelGGL((k_decode_self<DT, D, G, MP, GMAX, false, SPLIT>), grid, block, smem, st, f);
+}
+
+template <class DT, int D, int G, bool MP, bool GMAX>
+void launch_self(const FusedArgs& f, size_t smem, hipStream_t st) {
+  if (f.d.splits > 1)
+    launch_self_split<DT, D, G, MP, GMAX, true>(f, smem, st);
+  else
+    launch_self_split<DT, D, G, MP, GMAX, false>(f, smem, st);
 }
 
 template <class DT, int D, int G>
