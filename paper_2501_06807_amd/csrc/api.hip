@@ -631,6 +631,15 @@ mpc_status mpc_test_step_form(const mpc_dims* dims, int32_t Ts, int32_t n_tail, 
   return ok();
 }
 
+// The same of mpc_build_clusters and of the build in mpc_prefill: whether small super-clusters take a wave each.
+mpc_status mpc_test_build_form(const mpc_dims* dims, int32_t Ts, const mpc_select_cfg* cfg, int32_t* small) {
+  mpc::BuildArgs a;
+  const mpc_status s = prepare_build(dims, Ts, cfg, (const void*)256, (float*)256, (float*)256, &a);
+  if (s != MPC_OK) return s;
+  *small = mpc::small_build(a, mpc::kWave * 16 / (dims->head_dim * elt_size(dims->dtype)));
+  return ok();
+}
+
 mpc_status mpc_commonality(int32_t L, int32_t units, int32_t k, int32_t m, const int32_t* idx, double* out,
                            void* stream) {
   if (L <= 0 || units <= 0 || k <= 0 || m < 0) return fail(MPC_EINVAL, "L, units, k must be positive and m >= 0");

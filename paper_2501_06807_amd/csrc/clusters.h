@@ -30,6 +30,9 @@ struct BuildArgs {
   BuildGather g;      // prefill mode when g.kept is set (then Ts = keep, sup0 = 0, n_sup = S)
 };
 
+// Whether the build takes a wave per super-cluster (at most kSmallLoads loads of rpw rows, none shared by two clusters).
+bool small_build(const BuildArgs& a, int rpw);
+
 hipError_t launch_build(const BuildArgs& a, int dtype, int D, hipStream_t st);
 
 }  // namespace mpc

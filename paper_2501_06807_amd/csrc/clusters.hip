@@ -5,45 +5,36 @@
 // One workgroup per (owner layer, sequence, kv head, super-cluster), over all super-clusters or,
 // when a decode-time tail is sealed into a new cluster, over the one super-cluster that holds it.
 // Each wave streams the rows of one fine cluster at a time with coalesced 16-byte loads (LPR
-// lanes per row), reduces max / min over its row groups with lane swaps, writes the fine
+// lanes per row), reduces max / min over its row groups with cross-lane shuffles, writes the fine
 // representative and folds the bounds into its super-cluster bounds; the waves' super bounds meet
 // in LDS. In prefill mode a wave first reads the kept positions of up to 64 rows of its cluster
 // (one coalesced load) and takes each row's position from its lane; every row it reads from the
 // prompt cache is also written, with its value row, to the kept cache. Max / min are exact,
 // the linear representative is two fp32 products and one fp32 sum with no contraction, and the
-// average's fp64 sums of 16-bit keys are exact, so their order does not matter. Small super-clusters take a
-// wave each (k_build_small).
+// average's fp64 sums of 16-bit keys are exact, so their order does not matter. Small super-clusters, where there
+// are many, take a wave each (k_build_small).
 #include "clusters.h"
 
 namespace mpc {
 namespace {
 
-// Bounds (or sums) of a wave's row groups: every lane receives those of its columns over all rows.
+// Bounds (or sums) of a wave's row groups: every lane receives those of its columns over all rows. By shuffles, which
+// run on the LDS pipe beside the vector work that bounds a build from the kept cache; the lane swaps of gfx950 are vector
+// instructions (256 heads of 4096 rows of 256 B in clusters of four: 148 us with swaps, 133 so).
 template <int LPR, int EPL, bool MEAN>
 __device__ __forceinline__ void meet(float (&mx)[EPL], float (&mn)[EPL], double (&sum)[EPL]) {
-  auto hi = [](float x, float y) { return fmaxf(x, y); };
-  auto lo = [](float x, float y) { return fminf(x, y); };
 #pragma unroll
-  for (int e = 0; e < EPL; ++e) {
-    if constexpr (MEAN) {
+  for (int o = LPR; o < kWave; o <<= 1) {
 #pragma unroll
-      for (int o = LPR; o < kWave; o <<= 1) sum[e] += __shfl_xor(sum[e], o);
-    } else {
-      if constexpr (LPR <= 8) {
-        mx[e] = xor_combine<8>(mx[e], hi);
-        mn[e] = xor_combine<8>(mn[e], lo);
-      }
-      if constexpr (LPR <= 16) {
-        mx[e] = xor_combine<16>(mx[e], hi);
-        mn[e] = xor_combine<16>(mn[e], lo);
-      }
-      if constexpr (LPR <= 32) {
-        mx[e] = xor_combine<32>(mx[e], hi);
-        mn[e] = xor_combine<32>(mn[e], lo);
+    for (int e = 0; e < EPL; ++e) {
+      if constexpr (MEAN) {
+        sum[e] += __shfl_xor(sum[e], o);
+      } else {
+        mx[e] = fmaxf(mx[e], __shfl_xor(mx[e], o));
+        mn[e] = fminf(mn[e], __shfl_xor(mn[e], o));
       }
     }
   }
-  static_assert(LPR == 8 || LPR == 16 || LPR == 32, "lanes per row");
 }
 
 // A lane's columns of a representative over n_tok tokens.
@@ -66,8 +57,8 @@ __device__ __forceinline__ void put_rep(float* out, float alpha, float beta, con
 
 // Small super-clusters (at most four row loads): a wave takes a whole super-cluster, with all its rows
 // requested before any is folded and no barrier. With a workgroup per super-cluster, clusters of four tokens in
-// pairs left half of the waves idle and each load waiting for its position, and the row groups met through
-// LDS shuffles: 17 owner layers of 256 heads, 512 kept rows each, 720 us; 517 us so (2.7 GB moved, 5.2 TB/s).
+// pairs left half of the waves idle and each load waiting for its position: 17 owner layers of 256 heads, 512 kept
+// rows each, 720 us; 494 us so (2.7 GB moved, 5.5 TB/s).
 constexpr int kSmallLoads = 4;
 
 template <class DT, int D, int NW, int SIM, bool GATHER>
@@ -321,9 +312,7 @@ template <class DT, int D, int SIM, bool GATHER>
 void launch_shape(const BuildArgs& a, hipStream_t st) {
   constexpr int NW = 4, RPW = kWave * DT::kVec / D;  // rows per load of a wave
   const int heads = a.own.n * a.B * a.Hkv;
-  // a wave per super-cluster when it is at most kSmallLoads loads, none of which two clusters share, and
-  // there is more than one to a head (a sealed tail rebuilds one)
-  if (a.f <= kSmallLoads * RPW / a.s && a.s % RPW == 0 && a.n_sup > 1)
+  if (small_build(a, RPW))
     hipLaunchKernelGGL((k_build_small<DT, D, NW, SIM, GATHER>), dim3(heads * ((a.n_sup + NW - 1) / NW)), dim3(NW * kWave),
                        0, st, a);
   else
@@ -360,6 +349,18 @@ hipError_t launch_dt(const BuildArgs& a, int D, hipStream_t st) {
 }
 
 }  // namespace
+
+// A wave takes its clusters one after the other, which only many super-clusters hide. Up to two clusters leave half of a
+// workgroup idle, so from as many super-clusters on as workgroups are resident at once (eight to a compute unit);
+// three or four only from the size on where the whole build is bound by its instructions. A sealed tail rebuilds one
+// super-cluster per head, which a workgroup of such waves would leave idle. Builds from the kept cache, us, a workgroup
+// and a wave per super-cluster: pairs of four tokens of 256 B, 512 super-clusters 3.7 and 4.1, 2048 5.5 and 4.9, 131072
+// 187 and 120; fours of eight tokens of 128 B, 4096 13.3 and 13.1 (gathered, with the passes, 49.3 and 53.8), 32768 77.5
+// and 70.6 (259 and 248); fours of four of 256 B, 128 3.3 and 5.3, 65536 133 and 116.
+bool small_build(const BuildArgs& a, int rpw) {
+  return a.f <= kSmallLoads * rpw / a.s && a.s % rpw == 0 && a.n_sup > 1 &&
+         (int64_t)a.own.n * a.B * a.Hkv * a.n_sup >= (a.f <= 2 ? 8 : 128) * (int64_t)kNumCU;
+}
 
 hipError_t launch_build(const BuildArgs& a, int dtype, int D, hipStream_t st) {
   switch (dtype) {

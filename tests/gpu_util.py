@@ -88,3 +88,13 @@ def step_form(dims, Ts, cfg, n_tail=0):
                                    ctypes.byref(splits), ctypes.byref(waves))
     assert s == 0, L.lib().mpc_last_error()
     return FORMS[form.value], splits.value, waves.value
+
+
+def build_form(dims, Ts, cfg):
+    """Whether a cluster build of these sizes takes a wave per super-cluster. No GPU needed."""
+    import ctypes
+
+    from paper_2501_06807_amd import _lib as L
+    small = ctypes.c_int32()
+    assert L.lib().mpc_test_build_form(ctypes.byref(dims), Ts, ctypes.byref(cfg), ctypes.byref(small)) == 0, L.lib().mpc_last_error()
+    return bool(small.value)
