@@ -125,8 +125,8 @@ DecodeWs decode_ws(const mpc_dims* d, bool per_q_head) {
   const int G = d->n_q_heads / heads;
   const mpc::DecodePlan p = mpc::decode_plan(units, 1 << 30, 1, d->head_dim, elt_size(d->dtype), G);
   DecodeWs w{0, 0};
-  if (p.splits <= 1) return w;
-  w.cnt = align256((size_t)units * p.splits * G * (d->head_dim + 2) * sizeof(float));
+  if (p.most <= 1) return w;
+  w.cnt = align256((size_t)units * p.most * G * (d->head_dim + 2) * sizeof(float));
   w.total = w.cnt + align256((size_t)units * sizeof(int));
   return w;
 }

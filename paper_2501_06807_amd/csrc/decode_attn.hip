@@ -86,20 +86,30 @@ DecodePlan decode_plan(int units, int n_slot, int s, int D, int elt, int G) {
     p.most = (2 * kNumCU + units - 1) / units;
     if (p.most > max_splits) p.most = max_splits;
     if (p.most > kMaxSplits) p.most = kMaxSplits;
-    // A split pays for its partial's stores, the arrival and the merge (three memory round trips, about
-    // 3 us), so each gets at least 64 KiB of K rows, less where a row serves more query heads than two
-    // (its arithmetic then weighs more). Measured, us per launch, splits in parentheses:
+    // Cost of a split count in twentieths of a step (a workgroup's pass over its rows, about 1.15 us): the steps, dearer
+    // where a compute unit holds several workgroups, and for a split its partial's stores, the arrival and the merge
+    // (three memory round trips, about two steps). So lists of up to three steps stay whole, longer ones become splits of
+    // one step while each has a compute unit to itself. The weights are a fit to 900 measured blocks of 1 to 240 units
+    // and 128 to 3200 rows of all types, both head dims and 1 to 8 query heads (attention within 2% of the best count on
+    // average). us per launch, splits in parentheses:
     //   32 units of 384 rows of 256 B        8.9 (12)   6.2 (3)   5.7 (1)
-    //   32 units of 1632 rows of 256 B      10.5 (16)   9.1 (6)  11.2 (3)
-    //   64 units of 384 rows of 512 B        8.3 (8)    7.8 (3)  10.5 (1)
+    //   32 units of 1600 rows of 256 B       9.5 (16)   8.4 (7)  11.1 (3)  17.9 (1)
+    //   128 units of 400 rows of 256 B, G=4 10.0 (4)   12.2 (3)   9.4 (2)  10.0 (1)  (fp32)
     //   144 units of 128 rows of 128 B       7.0 (4)    4.4 (1)
-    //   8 units of 640 rows of 256 B, G = 4 10.1 (16)   9.3 (5)  11.5 (2)  12.1 (1)
-    //   8 units of 960 rows of 256 B, G = 8 16.2 (16)  17.2 (7)  20.6 (3)  34.5 (1)
-    int least = (64 << 10) / (D * elt);
-    if (G > 2) least /= G / 2;
-    p.splits = n_slot / least;
-    if (p.splits > p.most) p.splits = p.most;
-    if (p.splits < 1) p.splits = 1;
+    //   4 units of 1600 rows of 256 B        6.4 (14)   7.9 (6)  13.3 (1)
+    //   1 unit of 640 rows of 256 B          6.1 (16)   5.5 (5)   6.9 (1)
+    const int64_t step = G == 4 && elt == 2 ? p.waves * 16 : 4 * rows_per_pass;  // rows, as the kernels take them
+    int64_t best = 0;
+    for (int sp = 1; sp <= p.most; ++sp) {
+      const int per_cu = (units * sp + kNumCU - 1) / kNumCU;
+      int64_t cost = ((n_slot + sp - 1LL) / sp + step - 1) / step * (20 + 35 * (per_cu - 1));
+      if (sp > 1) cost += 37 + sp;
+      if (per_cu > 1) cost += 10;
+      if (sp == 1 || cost < best) {
+        best = cost;
+        p.splits = sp;
+      }
+    }
   }
   // Many units with short lists: a wave each. A workgroup's pass is 32 KiB of K rows (8 waves of 4 loads of
   // 1 KiB); a list of at most half of that leaves half of its lanes without a row, beside its barrier and the

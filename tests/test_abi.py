@@ -255,13 +255,21 @@ def test_decode_step_forms():
     def form(units, rows, dtype=2, group="sum", G=1, d=128):
         dims = _dims(n_layers=units, n_q_heads=G, n_kv_heads=1, head_dim=d, dtype=dtype) if units <= 256 else \
             _dims(n_layers=units // 8, n_q_heads=8 * G, n_kv_heads=8, head_dim=d, dtype=dtype)
-        cfg = L.select_cfg(16, 4, 32, rows // 16, share_period=1, group=group)
-        return step_form(dims, 2048, cfg)
+        cfg = L.select_cfg(16, 4, 64, rows // 16, share_period=1, group=group)
+        return step_form(dims, 4096, cfg)
 
     assert form(256, 1024) == ("self-selecting", 1, 8)
+    assert form(32, 384) == ("self-selecting", 1, 8)       # three steps of a workgroup
+    assert form(32, 400) == ("self-selecting", 4, 8)
     assert form(128, 512) == ("self-selecting", 2, 8)      # 256 workgroups
-    assert form(136, 512) == ("two kernels", 2, 8)         # 272
-    assert form(86, 768) == ("two kernels", 3, 8)          # 258
+    assert form(136, 512) == ("self-selecting", 1, 8)      # no room for a second
+    assert form(144, 3200, dtype=0) == ("two kernels", 3, 8)  # 432: two to a compute unit
+    assert form(8, 192, dtype=0, G=8) == ("self-selecting", 1, 8)
+    assert form(8, 208, dtype=0, G=8) == ("self-selecting", 4, 8)
+    assert form(8, 384, G=4, d=64) == ("self-selecting", 1, 8)  # matrix-core scores: 128 rows a step of either width
+    assert form(8, 400, G=4, d=64) == ("self-selecting", 4, 8)
+    assert form(8, 768, G=2, d=64) == ("self-selecting", 1, 8)
+    assert form(8, 784, G=2, d=64) == ("self-selecting", 4, 8)
     assert form(264, 256) == ("claiming", 1, 8)            # 64 KiB a list
     assert form(264, 240) == ("two kernels", 1, 8)
     assert form(512, 256) == ("claiming", 1, 8)

@@ -16,13 +16,13 @@ CASES = {
     "C3-L8": ("C3", dict(n_layers=8)),
     # 32 units in several splits: the same with split attention (its arrival counts back at zero after every launch)
     "C3-L1-long": ("C3", dict(n_layers=1, k_clusters=40)),
-    # 128 units in three splits: the two kernels in turn, the attention split over workgroups
-    "C3-L4-long": ("C3", dict(n_layers=4, k_clusters=24)),
+    # 160 units of 3840 fp32 rows in three splits: the two kernels in turn, the attention split over workgroups
+    "C3-L5-long": ("C3", dict(n_layers=5, dtype="fp32", k_super=16, k_clusters=120)),
     # 512 units: the claiming one-launch kernel (its workspace words back at zero after every launch)
     "C3-L16": ("C3", dict(n_layers=16)),
 }
 FORM = {"C2": ("self-selecting", 1), "C3-L8": ("self-selecting", 1), "C3-L1-long": ("self-selecting", 5),
-        "C3-L4-long": ("two kernels", 3), "C3-L16": ("claiming", 1)}
+        "C3-L5-long": ("two kernels", 3), "C3-L16": ("claiming", 1)}
 
 
 def _inputs(w, steps=3):
