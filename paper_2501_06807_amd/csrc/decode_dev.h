@@ -132,52 +132,43 @@ __device__ __forceinline__ void finish_unit(const DecodeArgs& a, int unit, int s
   }
 }
 
-// Attention of one work unit (or one split of it). COH_SEL: read the selection with
-// device-coherent loads (it was written by another workgroup of the same launch). The gathered V
-// rows are loaded with the non-temporal hint; the K rows too when STREAM_K.
-template <class DT, int D, int G, int NW, int U, bool COH_SEL, bool STREAM_K>
-__device__ __forceinline__ void attend_unit(const DecodeArgs& a, int unit, int split, const int32_t* pick) {
+// A unit's queries as the lane's columns meet them. 16-bit types: packed, for the two-wide dot instructions (exact bf16 /
+// fp16 products, fp32 sums, scaled afterwards); fp32: scaled, for fused multiply-adds.
+template <class DT, int D, int G>
+struct UnitQuery {
+  static constexpr int EPL = DT::kVec;
+  static constexpr bool kDot2 = DT::kElt == 2;
+  uint4 raw[G];
+  float f[G][EPL];
+  __device__ __forceinline__ UnitQuery(const DecodeArgs& a, size_t q_row0, int li) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      raw[g] = ldg16((const char*)a.q + ((q_row0 + g) * D + li * EPL) * DT::kElt);
+      if constexpr (!kDot2) {
+        float t[EPL];
+        unpack<DT>(raw[g], t);
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) f[g][e] = t[e] * a.qscale;
+      }
+    }
+  }
+};
+
+// Online softmax of slots [lo, hi) of the list s_sel by the row layout: wave w of NW, RPW rows a load, U loads a step.
+// Every lane ends with the (m, l) of its row group's rows and its columns of their weighted sum.
+template <class DT, int D, int G, int NW, int U, bool STREAM_K>
+__device__ __forceinline__ void attend_rows(const DecodeArgs& a, int unit, const UnitQuery<DT, D, G>& q,
+                                            const int32_t* s_sel, int n_list, int lo, int hi, int w, float (&m)[G],
+                                            float (&l)[G], float (&acc)[G][DT::kVec]) {
   constexpr int EPL = DT::kVec;
   constexpr int LPR = D / EPL;
   constexpr int RPW = kWave / LPR;
   constexpr bool kDot2 = DT::kElt == 2;
   constexpr float kSlack = 8.f;
-  static_assert(LPR <= kWave && kWave % LPR == 0, "row must fit a wave");
-
-  __shared__ int32_t s_sel[kMaxSel];
-  __shared__ float s_m[NW][G], s_l[NW][G];
-  __shared__ float s_acc[NW][G][D];
-
-  const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
-  const int rg = lane / LPR, li = lane % LPR;
-
-  // unit = (l * B + b) * Hkv + h ; q-heads h*G .. h*G+G-1 of the same (l, b)
-  const size_t q_row0 = (size_t)(unit / a.Hkv) * a.Hq + (size_t)(unit % a.Hkv) * G;
-  // 16-bit types: q stays packed and the dot products use the two-wide dot instructions (exact
-  // bf16 / fp16 products, fp32 sums), scaled afterwards; fp32: q pre-scaled, fused multiply-adds
-  uint4 qraw[G];
-  float qf[G][EPL];
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    qraw[g] = ldg16((const char*)a.q + ((q_row0 + g) * D + li * EPL) * DT::kElt);
-    if constexpr (!kDot2) {
-      float t[EPL];
-      unpack<DT>(qraw[g], t);
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) qf[g][e] = t[e] * a.qscale;
-    }
-  }
-  // the cluster list after the query loads, so that both are in flight together
-  const int n_list = load_list<NW, COH_SEL>(a, unit, s_sel, pick);
-  __syncthreads();
-
-  const int n_slot = n_list * a.s, rows_end = a.Ts + a.n_tail;
-  const int chunk = (n_slot + a.splits - 1) / a.splits;
-  const int lo = split * chunk, hi = min(n_slot, lo + chunk);
+  const int lane = threadIdx.x % kWave, rg = lane / LPR, li = lane % LPR;
+  const int rows_end = a.Ts + a.n_tail;
   const char* kbase = (const char*)a.k + cache_offset<D, DT>(a, unit);
   const char* vbase = (const char*)a.v + cache_offset<D, DT>(a, unit);
-
-  float m[G], l[G], acc[G][EPL];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     m[g] = -1e30f;
@@ -233,13 +224,13 @@ __device__ __forceinline__ void attend_unit(const DecodeArgs& a, int unit, int s
       for (int g = 0; g < G; ++g) {
         float p = 0.f;
         if constexpr (kDot2) {
-          p = dot2<DT>(qraw[g].x, kr[u].x, p);
-          p = dot2<DT>(qraw[g].y, kr[u].y, p);
-          p = dot2<DT>(qraw[g].z, kr[u].z, p);
-          p = dot2<DT>(qraw[g].w, kr[u].w, p);
+          p = dot2<DT>(q.raw[g].x, kr[u].x, p);
+          p = dot2<DT>(q.raw[g].y, kr[u].y, p);
+          p = dot2<DT>(q.raw[g].z, kr[u].z, p);
+          p = dot2<DT>(q.raw[g].w, kr[u].w, p);
         } else {
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) p += qf[g][e] * kf[e];
+          for (int e = 0; e < EPL; ++e) p += q.f[g][e] * kf[e];
         }
         p = group_sum<LPR>(p);
         if constexpr (kDot2) p *= a.qscale;
@@ -281,6 +272,36 @@ __device__ __forceinline__ void attend_unit(const DecodeArgs& a, int unit, int s
       }
     }
   }
+}
+
+// Attention of one work unit (or one split of it). COH_SEL: read the selection with
+// device-coherent loads (it was written by another workgroup of the same launch). The gathered V
+// rows are loaded with the non-temporal hint; the K rows too when STREAM_K.
+template <class DT, int D, int G, int NW, int U, bool COH_SEL, bool STREAM_K>
+__device__ __forceinline__ void attend_unit(const DecodeArgs& a, int unit, int split, const int32_t* pick) {
+  constexpr int EPL = DT::kVec;
+  constexpr int LPR = D / EPL;
+  static_assert(LPR <= kWave && kWave % LPR == 0, "row must fit a wave");
+
+  __shared__ int32_t s_sel[kMaxSel];
+  __shared__ float s_m[NW][G], s_l[NW][G];
+  __shared__ float s_acc[NW][G][D];
+
+  const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
+  const int rg = lane / LPR, li = lane % LPR;
+
+  // unit = (l * B + b) * Hkv + h ; q-heads h*G .. h*G+G-1 of the same (l, b)
+  const size_t q_row0 = (size_t)(unit / a.Hkv) * a.Hq + (size_t)(unit % a.Hkv) * G;
+  const UnitQuery<DT, D, G> q(a, q_row0, li);
+  // the cluster list after the query loads, so that both are in flight together
+  const int n_list = load_list<NW, COH_SEL>(a, unit, s_sel, pick);
+  __syncthreads();
+
+  const int n_slot = n_list * a.s;
+  const int chunk = (n_slot + a.splits - 1) / a.splits;
+  const int lo = split * chunk, hi = min(n_slot, lo + chunk);
+  float m[G], l[G], acc[G][EPL];
+  attend_rows<DT, D, G, NW, U, STREAM_K>(a, unit, q, s_sel, n_list, lo, hi, w, m, l, acc);
 
   // merge the RPW row groups of the wave
 #pragma unroll
@@ -318,25 +339,10 @@ template <class DT, int D, int G, int U, bool STREAM_K>
 __device__ __forceinline__ void attend_wave(const DecodeArgs& a, int unit, int32_t* s_sel) {
   constexpr int EPL = DT::kVec;
   constexpr int LPR = D / EPL;
-  constexpr int RPW = kWave / LPR;
-  constexpr bool kDot2 = DT::kElt == 2;
-  constexpr float kSlack = 8.f;
-  constexpr int STEP = RPW * U;
 
   const int lane = threadIdx.x % kWave, rg = lane / LPR, li = lane % LPR;
   const size_t q_row0 = (size_t)(unit / a.Hkv) * a.Hq + (size_t)(unit % a.Hkv) * G;
-  uint4 qraw[G];
-  float qf[G][EPL];
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    qraw[g] = ldg16((const char*)a.q + ((q_row0 + g) * D + li * EPL) * DT::kElt);
-    if constexpr (!kDot2) {
-      float t[EPL];
-      unpack<DT>(qraw[g], t);
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) qf[g][e] = t[e] * a.qscale;
-    }
-  }
+  const UnitQuery<DT, D, G> q(a, q_row0, li);
   const int n_list = a.k_sel + (a.n_tail + a.s - 1) / a.s;
   if (lane < n_list) {
     int c = a.C + (lane - a.k_sel);
@@ -349,98 +355,8 @@ __device__ __forceinline__ void attend_wave(const DecodeArgs& a, int unit, int32
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
 
-  const int n_slot = n_list * a.s, rows_end = a.Ts + a.n_tail;
-  const char* kbase = (const char*)a.k + cache_offset<D, DT>(a, unit) + li * 16;
-  const char* vbase = (const char*)a.v + cache_offset<D, DT>(a, unit) + li * 16;
   float m[G], l[G], acc[G][EPL];
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    m[g] = -1e30f;
-    l[g] = 0.f;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
-  }
-  // slot cursors (cluster position, row), advanced by STEP slots without a division
-  int cpos[U], crow[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int sl = u * RPW + rg;
-    cpos[u] = sl / a.s;
-    crow[u] = sl % a.s;
-  }
-  const int step_pos = STEP / a.s, step_row = STEP % a.s;
-  for (int base = 0; base < n_slot; base += STEP) {
-    uint4 kr[U], vr[U];
-    bool ok[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int c = s_sel[min(cpos[u], n_list - 1)];
-      const int r = c * a.s + crow[u];
-      ok[u] = (base + u * RPW + rg < n_slot) & (c >= 0) & (r < rows_end);
-      const unsigned off = (unsigned)(ok[u] ? r : 0) * (unsigned)(D * DT::kElt);
-      kr[u] = kv_load<STREAM_K>(kbase + off);
-      vr[u] = kv_load<true>(vbase + off);
-      crow[u] += step_row;
-      cpos[u] += step_pos;
-      if (crow[u] >= a.s) {
-        crow[u] -= a.s;
-        ++cpos[u];
-      }
-    }
-    float sc[U][G];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      float kf[EPL];
-      if constexpr (!kDot2) unpack<DT>(kr[u], kf);
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        float p = 0.f;
-        if constexpr (kDot2) {
-          p = dot2<DT>(qraw[g].x, kr[u].x, p);
-          p = dot2<DT>(qraw[g].y, kr[u].y, p);
-          p = dot2<DT>(qraw[g].z, kr[u].z, p);
-          p = dot2<DT>(qraw[g].w, kr[u].w, p);
-        } else {
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) p += qf[g][e] * kf[e];
-        }
-        p = group_sum<LPR>(p);
-        if constexpr (kDot2) p *= a.qscale;
-        sc[u][g] = ok[u] ? p : -INFINITY;
-      }
-    }
-    float mx[G];
-    bool up = false;
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      mx[g] = m[g];
-#pragma unroll
-      for (int u = 0; u < U; ++u) mx[g] = fmaxf(mx[g], sc[u][g]);
-      up |= mx[g] > m[g] + kSlack;
-    }
-    if (__any(up)) {
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const float r = fast_exp2(m[g] - mx[g]);
-        l[g] *= r;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[g][e] *= r;
-        m[g] = mx[g];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      float vf[EPL];
-      unpack<DT>(vr[u], vf);
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const float p = fast_exp2(sc[u][g] - m[g]);
-        l[g] += p;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[g][e] += p * vf[e];
-      }
-    }
-  }
+  attend_rows<DT, D, G, 1, U, STREAM_K>(a, unit, q, s_sel, n_list, 0, n_list * a.s, 0, m, l, acc);
   // the row groups meet at the largest maximum
   auto hi = [](float x, float y) { return fmaxf(x, y); };
   auto add = [](float x, float y) { return x + y; };
