@@ -134,7 +134,7 @@ DecodeWs decode_ws(const mpc_dims* d, bool per_q_head) {
 size_t decode_ws_bytes(const mpc_dims* d) { return std::max(decode_ws(d, false).total, decode_ws(d, true).total); }
 
 // Fused decode-step workspace: the error word, per-owner-head state and consumer counts, then the
-// split-K partials used when the block is too small for the fused kernel.
+// split-K partials.
 struct StepWs {
   size_t state, cons, part, total;
 };

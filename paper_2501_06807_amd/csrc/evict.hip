@@ -414,10 +414,16 @@ __global__ __launch_bounds__(WAVES* kWave) void k_colsum(EvictArgs a) {
 // higher (the running sums rescaled by an exact power of two) and the block is summed again. The
 // four lanes of a row meet once at the end at the smallest offset, so no exponent of pass 2 exceeds 1.
 //
-// 32x32x16 blocks in a written-out order, with their offsets checked once per tile of 64 keys, were 2 to 8% faster
-// (a prefill of 32 x 8192 keys) only while exponents up to 5 were let through, which doubled the largest
-// error of a score on peaked rows. Held to exponents of at most 1 they were no faster (eviction of eight layers of 8192
-// keys and 32 heads: 1880 us here, 1898 us so; with scores of three times the spread 1944 and 2104 us).
+// 32x32x16 blocks in a written-out order, with their offsets checked once per tile of 64 keys, were faster (a prefill of
+// 32 x 8192 keys by 5%, of 12 layers of 2048 keys of 64 channels by a fifth) only while exponents up to 5 were let
+// through, which doubled the largest error of a score on peaked rows. Held to exponents of at most 1 they were no
+// faster (eviction of eight layers of 8192 keys and 32 heads: 1880 us here, 1898 us so; with scores of three times the
+// spread 1944 and 2104 us).
+//
+// What bounds it beside the column pass's causes: the slow path. The four lanes of a row keep offsets of their own, and in
+// the first tiles of a row or split a wave often holds a lane whose block exceeds its own: 84 heads of 2048 keys of
+// 64 channels in three splits run it in about a quarter of the blocks, at twice the column pass's vector
+// instructions (44 and 27 us).
 template <class DT, int D>
 __global__ __launch_bounds__(kRowThreads16, 3) void k_rowstats16(EvictArgs a) {
   constexpr int NT = kRowThreads16;
@@ -617,10 +623,11 @@ __global__ __launch_bounds__(kMergeThreads) void k_rowmerge(EvictArgs a) {
 // a barrier, a tile load and a row-statistics stash serve 64 rows. A lane holds rows
 // 4 (lane / 16) + r of one key per block; its fp32 sum over a tile's sixteen rows goes into an fp64
 // total, and the four lanes of a key meet once at the end.
-// What bounds it: the chip's power, as for the row pass (4 x 32768 keys, 32 heads: 3.3 ms, the matrix cores
-// busy 52% at 1.95 GHz). So the row pass's written-out order changes nothing here (fewer cycles at a lower
-// clock; 8192 keys to 131072 within 0.3%), and 32x32x16 blocks, which need 222 registers with the row
-// statistics of their sixteen rows a lane, are slower (two waves per SIMD: 3.7 against 3.3 ms). Quarters of a
+// What bounds it: matrix and vector work that overlap only in part, at the 1.9 GHz that the chip keeps under this load
+// (4 x 32768 keys, 32 heads: 3.3 ms, the matrix cores busy 51% of the cycles; 45% in the row pass, 3.7 ms). A written-out
+// order of the blocks changes nothing (fewer cycles at a lower clock; 8192 keys to 131072 within 0.3%), and 32x32x16
+// blocks, which need 222 registers with the row statistics of their sixteen rows a lane, are slower (two waves per
+// SIMD: 3.7 against 3.3 ms). Quarters of a
 // masked tile that no key of the wave is seen by, or past the window, are left out: of a window of 204 rows
 // the last tile holds 12 (8 x 1024 keys, 17 owner layers: 490 -> 467 us).
 template <class DT, int D>
